@@ -81,7 +81,9 @@ typedef struct p3m_params {
                              keeps the reactions as partials, of which the plan
                              holds pair_partials per particle (80 suits strongly
                              clustered sets); a call that needs more falls back
-                             to both sides. Pays on clustered sets (256^3
+                             to both sides, and so do forces on up to 3 2^20 and
+                             adjoints of up to 3 2^17 particles, where both sides
+                             are faster. Pays on large clustered sets (256^3
                              Plummer mix: -11 %), not on smooth ones            */
 } p3m_params;
 

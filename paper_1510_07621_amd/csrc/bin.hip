@@ -216,9 +216,9 @@ k_scan_add(int32_t* __restrict__ out, int64_t len, const int32_t* __restrict__ t
 
 // ---- pair-loop work list ----
 
-// Chunks of one i-group: its particles (G x G z-runs of G cells) over kChunk.
+// Chunks of one i-group: its particles (G x G z-runs of G cells) over the chunk.
 __device__ __forceinline__ int group_chunks(const int32_t* __restrict__ start, int lg, int G,
-                                            int lgG, int64_t g) {
+                                            int lgG, int64_t g, int chunk) {
   const int lgd = lg - lgG, md = (1 << lgd) - 1;
   int gz = (int)(g & md), gy = (int)((g >> lgd) & md), gx = (int)(g >> (2 * lgd));
   int cnt = 0;
@@ -227,18 +227,18 @@ __device__ __forceinline__ int group_chunks(const int32_t* __restrict__ start, i
       int c0 = ((((gx * G + a) << lg) | (gy * G + b)) << lg) | (gz * G);
       cnt += start[c0 + G] - start[c0];
     }
-  return (cnt + kChunk - 1) / kChunk;
+  return (cnt + chunk - 1) / chunk;
 }
 
 // Work list, pass 1: chunk counts of a tile of kThreads groups (one per
 // thread), their exclusive scan within the tile (goff) and the tile total.
 __global__ void __launch_bounds__(kThreads)
-k_items_tiles(const int32_t* __restrict__ start, int lg, int G, int lgG, int64_t ngroup,
+k_items_tiles(const int32_t* __restrict__ start, int lg, int G, int lgG, int64_t ngroup, int chunk,
               int32_t* __restrict__ gchunk, int32_t* __restrict__ goff,
               int32_t* __restrict__ tile_sum) {
   __shared__ int wsum[kThreads / 64];
   const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int v = g < ngroup ? group_chunks(start, lg, G, lgG, g) : 0;
+  const int v = g < ngroup ? group_chunks(start, lg, G, lgG, g, chunk) : 0;
   int total;
   const int ex = block_exclusive(v, wsum, total);
   if (g < ngroup) {
@@ -316,13 +316,53 @@ hipError_t launch_bin(p3m_plan* P, int64_t n, const double* pos, const double* m
   return hipGetLastError();
 }
 
-hipError_t launch_items(p3m_plan* P) {
+// How a call's particles are cut into work items: chunks of `chunk`
+// i-particles, each summed by item_waves waves that share its stencil. A
+// whole item (64 particles, one wave) takes 200 to 400 us from end to end, so
+// a set with fewer items than wave slots leaves most of the chip idle and
+// lasts that long whatever its size; a cut item stages its stencil for fewer
+// particles, which costs more in all. Short-range force call (binning
+// included) against whole items, us:
+//   n <= 8192, 16 particles and 8 waves: 4096 on 16^3, FP32 290 -> 47
+//   n <= 65536, 4 waves and 32 particles (FP64, two i-particles a lane, 16):
+//     32768 on 32^3, FP32 332 -> 93, FP64 484 -> 179; adjoint FP32 419 -> 140
+//   n <= 393216, 2 waves and 32: 64^3 on 64^3, FP32 492 -> 395, force and
+//     adjoint FP64 2998 -> 2492 (80^3: 2 waves and 1 even)
+//   larger sets, 32 particles: their last items end sooner and their boxes
+//     clip more. Clustered 2M on 128^3: FP32 2971 -> 2875, adjoint 4722 ->
+//     4454; FP64 1M 2344 -> 2181, but a 128^3 lattice 6008 -> 6189, and at
+//     16.7M particles FP32 41.6 -> 43.1 ms: whole items above 3 2^20 (FP32)
+//     and 3 2^19 (FP64) particles.
+// Groups that are sparse (under 16 particles on average) have one item each,
+// enough of them to fill the chip: splitting those measured slower (FP32
+// 200001 on 128^3: 2 waves 304 -> 328 us).
+static void pair_split(p3m_plan* P, int64_t n) {
+  const bool f64 = P->prm.precision == P3M_FP64;
+  P->item_waves = 1;
+  P->chunk = n <= (int64_t{3} << (f64 ? 19 : 20)) ? 32 : kChunk;
+  if (n >= 16 * P->ngroup) {
+    if (n <= 8192) {
+      P->item_waves = 8;
+      P->chunk = 16;
+    } else if (n <= 65536) {
+      P->item_waves = 4;
+      if (f64) P->chunk = 16;
+    } else if (n <= 393216) {
+      P->item_waves = 2;
+    }
+  }
+}
+
+hipError_t launch_items(p3m_plan* P, int64_t n, bool whole) {
   Workspace& W = P->ws;
+  P->chunk = kChunk;
+  P->item_waves = 1;
+  if (!whole) pair_split(P, n);
   hipStream_t s = P->stream;
   // chunk counts + tile scans, scan of the tile sums (total to goff[ngroup]),
   // then the items at tile offset + offset within the tile
   const int nt = (int)((P->ngroup + kThreads - 1) / kThreads);
-  k_items_tiles<<<nt, kThreads, 0, s>>>(W.start, P->lg, P->G, P->lgG, P->ngroup, W.gchunk,
+  k_items_tiles<<<nt, kThreads, 0, s>>>(W.start, P->lg, P->G, P->lgG, P->ngroup, P->chunk, W.gchunk,
                                         W.goff, W.scan_tmp);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

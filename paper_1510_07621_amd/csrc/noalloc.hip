@@ -109,7 +109,7 @@ extern "C" int pp_force_noalloc(const p3m_params* params, int64_t n, const doubl
   carve(&P, base, n);
   if ((e = p3m::plan_upload_tables(&P, g_rows)) != hipSuccess) return status_of(e);
   if ((e = p3m::launch_bin(&P, n, pos, mass, mass_scalar)) != hipSuccess) return status_of(e);
-  if ((e = p3m::launch_items(&P)) != hipSuccess) return status_of(e);
+  if ((e = p3m::launch_items(&P, n, false)) != hipSuccess) return status_of(e);
   e = params->precision == P3M_FP32
           ? p3m::launch_pairs<float>(&P, n, false, force, force_fp32 ? 1 : 0, mass == nullptr)
           : p3m::launch_pairs<double>(&P, n, false, force, force_fp32 ? 1 : 0, mass == nullptr);

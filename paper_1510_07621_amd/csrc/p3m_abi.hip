@@ -105,6 +105,12 @@ void begin_call(p3m_plan* P) {
 
 enum class Part { kP3M, kPM, kPP };
 
+// A one-sided plan evaluates small sets from both sides all the same (see
+// kOneSidedMin).
+bool one_sided_call(const p3m_plan* P, int64_t n, bool vjp) {
+  return P->rcap > 0 && n > (vjp ? kOneSidedVjpMin : kOneSidedMin);
+}
+
 // Launches that take the plan's stream enqueue on `s` while this is alive.
 struct OnStream {
   p3m_plan* P;
@@ -117,11 +123,12 @@ template <typename T>
 hipError_t run_force(p3m_plan* P, int64_t n, const double* pos, const double* mass,
                      double ms, void* force, int f32, Part part) {
   hipError_t e;
-  const bool half = P->rcap > 0 && part != Part::kPM;
+  const bool half = part != Part::kPM && one_sided_call(P, n, false);
+  P->one_sided = half;
   {
     StageTimer t(P, P3M_STAGE_BIN);
     if ((e = launch_bin(P, n, pos, mass, ms)) != hipSuccess) return e;
-    if (part != Part::kPM && (e = launch_items(P)) != hipSuccess) return e;
+    if (part != Part::kPM && (e = launch_items(P, n, half)) != hipSuccess) return e;
     if (half && (e = launch_react_prepass(P)) != hipSuccess) return e;
   }
   if (part == Part::kP3M) {
@@ -222,11 +229,12 @@ hipError_t run_vjp(p3m_plan* P, int64_t n, const double* pos, const double* mass
                    const double* fbar, double* pbar, Part part) {
   hipError_t e;
   Workspace& W = P->ws;
-  const bool half = P->rcap > 0 && part != Part::kPM;
+  const bool half = part != Part::kPM && one_sided_call(P, n, true);
+  P->one_sided = half;
   {
     StageTimer t(P, P3M_STAGE_BIN);
     if ((e = launch_bin(P, n, pos, mass, ms)) != hipSuccess) return e;
-    if (part != Part::kPM && (e = launch_items(P)) != hipSuccess) return e;
+    if (part != Part::kPM && (e = launch_items(P, n, half)) != hipSuccess) return e;
     if (half && (e = launch_react_prepass(P)) != hipSuccess) return e;
     if ((e = launch_lambda_sort<T>(P, n, fbar)) != hipSuccess) return e;
   }
@@ -602,7 +610,7 @@ int plan_geometry(const p3m_params& q, int64_t n_max, p3m_plan* P) {
   P->nrows = stencil_rows(P->G, r_c / h, nullptr, 0);
   P->nseg = segment_rows(P->G, r_c / h, nullptr, 0, &P->npos);
   if (P->nseg < 0) return P->nseg;
-  P->max_items = P->ngroup + (n_max + kChunk - 1) / kChunk;
+  P->max_items = P->ngroup + n_max / kMinChunk;
   P->scan_tmp_len = std::max(scan_tmp_size(P->ncell), items_tmp_size(P->ngroup));
   return P3M_OK;
 }
@@ -986,7 +994,7 @@ int p3m_pair_count(p3m_plan* P, int64_t n, const double* pos, int64_t* count_out
   if (n == 0) return status_of(launch_fill_i32((int32_t*)count_out, 2, 0, P->stream));
   P->timing_slot = -1;
   if ((e = launch_bin(P, n, pos, nullptr, 1.0)) != hipSuccess) return status_of(e);
-  if ((e = launch_items(P)) != hipSuccess) return status_of(e);
+  if ((e = launch_items(P, n, true)) != hipSuccess) return status_of(e);
   e = P->prm.precision == P3M_FP32 ? launch_pair_count<float>(P, n, count_out)
                                    : launch_pair_count<double>(P, n, count_out);
   return status_of(e);

@@ -24,6 +24,16 @@ template <> struct Vec<double> {
 constexpr int kPairCap = 128;     // j-particles staged in LDS per pass of the pair loop
 constexpr int kBrick = 8;         // cells per brick edge (deposit, interpolation)
 constexpr int kChunk = 64;        // i-particles per pair-loop work item (one wavefront)
+constexpr int kMinChunk = 16;     // the smallest chunk that small sets are cut into
+// Calls of up to this many particles evaluate every pair from both sides
+// also in a one-sided plan: the two-sided sum's items can be cut as small as
+// the set asks for (pair_split), the one-sided sum's follow its partials.
+// Clustered sets, two- against one-sided, force call in ms: 32769 on 32^3
+// FP32 0.13, 0.36; 500001 on 64^3 FP32 1.21, 1.32; 2M on 128^3 FP32 2.97,
+// 3.48, FP64 7.3, 9.2; 16.7M on 256^3 FP32 45.2, 40.2. Adjoint: 262145 on
+// 64^3 FP32 0.72, 0.92, FP64 1.66, 2.01; 500001 on 64^3 FP64 4.95, 4.75.
+constexpr int64_t kOneSidedMin = int64_t{3} << 20;
+constexpr int64_t kOneSidedVjpMin = int64_t{3} << 17;
 constexpr int kXcds = 8;          // accelerator complex dies of an MI355X (one L2 each)
 constexpr int kSplitBins = 64;    // pieces of the split-factor tables
 constexpr int kSplitCoef64 = 7;   // coefficients per piece of the FP64 table (degree 6)
@@ -127,6 +137,10 @@ struct p3m_plan {
   int nseg = 0, npos = 0;       // stencil segments, and the positive ones
   int64_t rcap = 0;             // reaction partials the plan holds (0: two-sided sum only)
   int64_t max_items = 0;
+  // the pair loop's work items of the call in progress (pair_split)
+  int chunk = p3m::kChunk;      // i-particles per item
+  int item_waves = 1;           // waves that share an item's stencil
+  bool one_sided = false;       // pairs of dense groups once (one-sided plans)
   int tab_var = 0;              // FP32 split table: variable (0: r, 1: softened r)
   double tab_v0 = 0, tab_v1 = 0;  // and its range, as lengths
   int tab64_var = 0;            // FP64 split table: the same, and the number of
@@ -154,7 +168,9 @@ int items_tmp_size(int64_t ngroup);   // block sums of the work-list scan
 
 hipError_t launch_bin(p3m_plan* P, int64_t n, const double* pos, const double* mass,
                       double mass_scalar);
-hipError_t launch_items(p3m_plan* P);
+// The work list of n binned particles, cut as pair_split says (whole: in
+// chunks of kChunk, one wave each).
+hipError_t launch_items(p3m_plan* P, int64_t n, bool whole);
 
 template <typename T>
 hipError_t launch_deposit(p3m_plan* P);

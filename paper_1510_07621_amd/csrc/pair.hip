@@ -4,8 +4,10 @@
 //   f(r) = erfc(u) + (2u / sqrt(pi)) exp(-u^2),  u = r / (2 r_s)
 //
 // Work decomposition. The grid's cells are grouped into i-groups of G^3
-// cells; a work item is (group, chunk) with up to kChunk (64) of the
-// group's particles, one wavefront per item. The j-candidates of a group are the
+// cells; a work item is (group, chunk) with up to `chunk` (64; fewer for
+// smaller sets) of the group's particles, summed by one wavefront or, for
+// small sets, by a workgroup of 2 to 8 that share the stencil's rows (the
+// launch's rule and its figures: pair_split). The j-candidates of a group are the
 // particles of every cell whose box comes closer than r_c to the group's box
 // (the stencil rows: z-runs of cells, precomputed per plan).
 //
@@ -16,6 +18,9 @@
 // takes every s-th staged j, so small groups still fill the wave, and the s
 // partial sums of each i are added at the end. FP32: U = 8 above 32
 // particles, else 4; FP64: U = 2; U = 1 for an item with a single particle.
+// Up to U = 4 a two-sided item has as many streams as fill the wave (with at
+// most 16, an item of four particles kept 16 lanes busy: 300007 clustered
+// particles on 128^3, short-range call 356 -> 344 us).
 //
 // Staging. Per batch of 64 stencil rows each lane resolves one row into at
 // most three contiguous sorted runs (the z-run split where it crosses the
@@ -55,9 +60,8 @@ template <typename T, bool VJP> struct Stage {
   static constexpr int kCap = sizeof(T) == 4 && !VJP ? kPairCap : kPairCap / 2;
   static constexpr int kPer = kCap / 64;   // consecutive staged entries per lane
 };
-// At most kStreams streams, so kStreams far sentinels after the staged
-// entries cover every read past the end (an item with fewer than 64 / kStreams
-// slot sets leaves lanes idle; only items of a handful of particles).
+// At most kStreams streams (without clamped reads), so kStreams far sentinels
+// after the staged entries cover every read past the end.
 constexpr int kStreams = 16;
 // Waves per SIMD the compiler must leave room for (caps the registers).
 template <typename T, bool VJP>
@@ -73,6 +77,7 @@ struct PairArgs {
   const int32_t* __restrict__ start;
   const int2* __restrict__ items;
   const int32_t* __restrict__ n_items;
+  int chunk;                            // i-particles per item (kChunk in the one-sided sum)
   const int4* __restrict__ rows;
   int nrows;
   int ng, lg, G, lgG;
@@ -370,21 +375,46 @@ struct ItemBox {
 template <>
 struct ItemBox<double> {};     // the FP64 pair loop stages whole rows
 
+// Orders the LDS accesses of one wave (its own lanes only: the LDS takes a
+// wave's accesses in order, so no wait is needed, only that the compiler
+// keeps the order). The waves of a workgroup run their stages independently.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One wave's staging area.
 template <typename T, bool VJP, bool HALF>
-struct PairShared {
-  SplitTable<T> tab;                       // first, so one address register reaches
-                                           // all coefficient arrays
-  typename Vec<T>::v4 jb[Stage<T, VJP>::kCap + kStreams];   // staged j (+ far sentinels); reused for
-                                                // the reduction
+struct WaveShared {
+  typename Vec<T>::v4 jb[Stage<T, VJP>::kCap + kStreams];   // staged j (+ far sentinels)
   typename Vec<T>::v4 jl[VJP ? Stage<T, VJP>::kCap + kStreams : 1];   // adjoint mode: staged j cotangents
   int d_lo[kDesc], d_pre[kDesc + 1], d_zs[kDesc];
   int d_rp[HALF ? kDesc : 1];              // one-sided sum: partial offset of each run's
                                            // first entry in the item's reactions, or -1
   int owner[Stage<T, VJP>::kCap];               // run of each staged entry of a chunk
   int d_rx[64], d_ry[64];                  // x, y cell offsets of each row
-  int i_lo[16], i_pre[17];
   ItemBox<T> box;                          // the item's i-particles' bounding box
 };
+
+// A workgroup of W waves shares one item: the split table, the group's
+// z-runs and, for W > 1, the waves' sums per i-particle.
+template <typename T, bool VJP, bool HALF, int W>
+struct PairShared {
+  SplitTable<T> tab;                       // first, so one address register reaches
+                                           // all coefficient arrays
+  WaveShared<T, VJP, HALF> w[W];
+  int i_lo[16], i_pre[17];
+  T wsum[W > 1 ? W : 1][W > 1 ? 3 * kChunk : 1];
+};
+
+// The z-run of the group's flattened particle index fi: the largest run with
+// i_pre[run] <= fi (GG runs, a power of two).
+__device__ __forceinline__ int find_run(const int* i_pre, int GG, int fi) {
+  int run = 0;
+  for (int step = GG >> 1; step > 0; step >>= 1)
+    if (i_pre[run + step] <= fi) run += step;
+  return run;
+}
 
 // Sum of v over each aligned group of nu lanes (nu a power of two <= 32),
 // left in the group's top lane (lane % nu == nu - 1): pairwise sums inside
@@ -442,8 +472,8 @@ struct RowRuns {
 
 template <typename T>
 __device__ __forceinline__ RowRuns<T> resolve_rows(const PairArgs<T>& A, const int4* rows,
-                                                   int nrows, int rb, int lane, int gx0,
-                                                   int gy0, int gz0, const ItemBox<T>& B) {
+                                                   int nrows, int r, int gx0, int gy0, int gz0,
+                                                   const ItemBox<T>& B) {
   RowRuns<T> R;
   const int lg = A.lg, ng = A.ng, mask = ng - 1;
 #pragma unroll
@@ -451,8 +481,8 @@ __device__ __forceinline__ RowRuns<T> resolve_rows(const PairArgs<T>& A, const i
   R.rx = R.ry = R.rf = 0;
   int z0 = 0, z1 = -1;
   int4 row = make_int4(0, 0, 0, -1);
-  if (rb + lane < nrows) {
-    row = rows[rb + lane];
+  if (r < nrows) {
+    row = rows[r];
     z0 = row.z;
     z1 = row.w;
   }
@@ -552,13 +582,20 @@ __device__ __forceinline__ RowRuns<T> resolve_segments(const PairArgs<T>& A, int
 // else every pair from both sides over the full stencil. NU: the number of
 // slot sets of the one-sided sum (a power of two, fixed per instantiation so
 // that the sums over them are straight-line code).
-template <typename T, int U, bool COUNT, bool UM, int TAB, bool VJP, bool HALF, int NU,
+// W: the waves of the workgroup share the item, wave w taking stencil rows w,
+// w + W, ...; their sums are added in wave order at the end.
+template <typename T, int U, bool COUNT, bool UM, int TAB, bool VJP, bool HALF, int NU, int W,
           typename SH>
-__device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
+__device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
                                           int gy0, int gz0, int ibeg, int ni, int64_t g) {
   using T4 = typename Vec<T>::v4;
   constexpr int kCap = Stage<T, VJP>::kCap, kStage = Stage<T, VJP>::kPer;
-  const int lane = threadIdx.x;
+  static_assert(W == 1 || (!HALF && !COUNT), "split items: two-sided sums only");
+  const int lane = threadIdx.x & 63;
+  const int wave = W == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  auto& S = B0.w[wave];
+  const int* i_pre = B0.i_pre;
+  const int* i_lo = B0.i_lo;
   const int ng = A.ng, mask = ng - 1, lgG = A.lgG, G = A.G, GG = G * G;
   // The force over the softened-distance table runs on positions scaled by
   // the table's s (the bin coordinate then needs no extra multiply). An i
@@ -575,7 +612,10 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
   // slot sets; the one-sided sum sums each staged entry's reaction over the
   // sets, so their number is rounded up to a power of two (empty sets idle)
   const int nu = HALF ? NU : (ni + U - 1) / U;
-  const int ns = min(64 / nu, kStreams);  // streams
+  // streams: with few i-particles up to one per lane; the two-sided sum's
+  // reads past the stage's end are then clamped onto its first sentinel
+  constexpr bool CLAMP = !HALF && U <= 4;
+  const int ns = CLAMP ? 64 / nu : min(64 / nu, kStreams);
   const int il = lane % nu, st = lane / nu;
   const bool active = st < ns;
 
@@ -588,9 +628,8 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
     const int q = il + u * nu;            // particle of this slot within the chunk
     const bool has = active && q < ni;
     const int fi = ibeg + min(q, ni - 1);
-    int run = 0;
-    while (run + 1 < GG && S.i_pre[run + 1] <= fi) ++run;
-    si[u] = S.i_lo[run] + (fi - S.i_pre[run]);
+    const int run = find_run(i_pre, GG, fi);
+    si[u] = i_lo[run] + (fi - i_pre[run]);
     const T4 pi = A.rec[si[u]];
     const int czi = A.skey[si[u]] & mask;
     xi[u] = has ? coord(run >> lgG, pi.x) : T(kFar);
@@ -632,7 +671,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
       S.box.reach2 = (SC ? A.rc2s : A.rc2) * T(1.0002);
 
     }
-    __syncthreads();
+    wave_sync();
   }
   const ItemBox<T>& B = S.box;
   int npairs = 0;
@@ -644,7 +683,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
   int rstaged = 0;    // reaction entries staged so far (phase 2: the segments)
   if constexpr (HALF) {
     ptotal = *A.gtotal;
-    const int ntot = S.i_pre[GG];
+    const int ntot = i_pre[GG];
     const int L = A.rowoff[g * (A.npos + 1) + A.npos];
     const int a = ibeg / kChunk;
     ibase = A.gbase[g] + (long long)a * (ntot + L) - 32LL * a * (a + 1);
@@ -655,14 +694,14 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
   // phase 1: the item's own group (reactions for entries past its own
   // chunk, by position); phase 2: group segments (reactions for flagged runs).
   auto run_batch = [&](const RowRuns<T>& cur, int phase) {
-    __syncthreads();       // previous batch is done with the descriptors and jb
+    wave_sync();           // previous batch is done with the descriptors and jb
     const int tot_l = cur.cnt[0] + cur.cnt[1] + cur.cnt[2];
     const int inc = wave_inclusive(tot_l);
     int rtotal = 0;
     if (HALF && phase == 2) {
       const int rc = cur.rf ? cur.cnt[0] : 0;
       const int rinc = wave_inclusive(rc);
-      const int intra = S.i_pre[GG] - ibeg - ni;
+      const int intra = i_pre[GG] - ibeg - ni;
       S.d_rp[3 * lane] = cur.rf ? intra + rstaged + rinc - rc : -1;
       S.d_rp[3 * lane + 1] = S.d_rp[3 * lane + 2] = -1;
       rtotal = __builtin_amdgcn_readfirstlane(__shfl(rinc, 63, 64));
@@ -686,19 +725,19 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
 
     for (int c0 = 0; c0 < total; c0 += kCap) {
       const int cn = min(kCap, total - c0);
-      __syncthreads();     // descriptors visible; previous chunk done with jb
+      wave_sync();         // descriptors visible; previous chunk done with jb
       // owner[q] = run of chunk entry q: each run marks its first entry in the
       // chunk, then a prefix maximum over the chunk fills the rest
       const int q0 = kStage * lane;
 #pragma unroll
       for (int e = 0; e < kStage; ++e) S.owner[q0 + e] = -1;
-      __syncthreads();
+      wave_sync();
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         const int s = pre[k] - c0;
         if (cur.cnt[k] > 0 && s + cur.cnt[k] > 0 && s < cn) S.owner[max(s, 0)] = 3 * lane + k;
       }
-      __syncthreads();
+      wave_sync();
       int dd[kStage];
       {
         int run = -1;
@@ -758,7 +797,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
         far.w = T(0);
         if (lane < kStreams) S.jb[cn + lane] = far;
       }
-      __syncthreads();
+      wave_sync();
       // lane (set, stream) takes staged entries st, st + ns, ...; the trip
       // count is wave-uniform; reads past the end (at most ns - 1) hit the
       // sentinels, and empty slots sit at +kFar, so both fail the cutoff test.
@@ -770,13 +809,14 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
       const int iters = (cn + ns - 1) / ns;
       const int st_r = active ? st : 0;
       T4* jp = S.jb + st_r;
+      auto entry = [&](int t) { return CLAMP ? min(t * ns + st_r, cn) - st_r : t * ns; };
       const bool top = active && il == nu - 1;
       if constexpr (VJP) {
         // sentinel slots carry no cotangent; their separations fail the test
         const T4* lp = S.jl + st_r;
 #pragma unroll 2
         for (int t = 0; t < iters; ++t) {
-          const T4 pj = jp[t * ns];
+          const T4 pj = jp[entry(t)];
           const T4 lj = t * ns + st_r < cn ? lp[t * ns] : T4{};
           T rx = 0, ry = 0, rz = 0;
 #pragma unroll
@@ -785,7 +825,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
             const T r2 = dx * dx + dy * dy + dz * dz;
             if (r2 < (SC ? A.rc2s : A.rc2) && r2 > T(0)) {   // coincident: nothing
               T w1, w2;
-              pair_vjp_weights<TAB>(r2, A, S.tab, w1, w2);
+              pair_vjp_weights<TAB>(r2, A, B0.tab, w1, w2);
               const T lx = lxi[u] - lj.x, ly = lyi[u] - lj.y, lz = lzi[u] - lj.z;
               const T c = w2 * (dx * lx + dy * ly + dz * lz);
               const T tx = w1 * lx + c * dx, ty = w1 * ly + c * dy, tz = w1 * lz + c * dz;
@@ -832,15 +872,15 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
         // FP64 reads the next staged j while the current one is tested
         // (measured 3 % faster; FP32 gains nothing and spills more)
         constexpr bool PF = sizeof(T) == 8;
-        T4 pn = jp[0];
+        T4 pn = jp[entry(0)];
 #pragma unroll 2
         for (int t = 0; t < iters; ++t) {
           T4 pj;
           if constexpr (PF) {
             pj = pn;
-            pn = jp[min(t + 1, iters - 1) * ns];
+            pn = jp[entry(min(t + 1, iters - 1))];
           } else {
-            pj = jp[t * ns];
+            pj = jp[entry(t)];
           }
           const T jx = pj.x, jy = pj.y, jz = pj.z;
           T rx = 0, ry = 0, rz = 0;
@@ -861,9 +901,9 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
               } else {
                 T w;
                 if constexpr (RHO)
-                  w = pair_weight_rho(r2, A, S.tab);
+                  w = pair_weight_rho(r2, A, B0.tab);
                 else
-                  w = pair_weight<TAB>(r2, A, S.tab);
+                  w = pair_weight<TAB>(r2, A, B0.tab);
                 const T wa = UM ? w : w * pj.w;
                 ax[u] += wa * dx;
                 ay[u] += wa * dy;
@@ -893,7 +933,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
         // the chunk's reactions to their partials: each lane its own staged
         // entries (phase 1: those past the item's own chunk, at their
         // position; phase 2: those of runs that take reactions)
-        __syncthreads();
+        wave_sync();
         T* px = (T*)A.rpart;
 #pragma unroll
         for (int e = 0; e < kStage; ++e) {
@@ -921,12 +961,12 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
   };
 
   if constexpr (HALF) {
-    run_batch(own_group_runs<T>(S, lane, lgG, G, gz0, ibeg), 1);
+    run_batch(own_group_runs<T>(B0, lane, lgG, G, gz0, ibeg), 1);
     for (int rb = 0; rb < A.nseg; rb += 64)
       run_batch(resolve_segments<T>(A, rb, lane, gx0, gy0, gz0, B), 2);
   } else {
-    for (int rb = 0; rb < A.nrows; rb += 64)
-      run_batch(resolve_rows<T>(A, A.rows, A.nrows, rb, lane, gx0, gy0, gz0, B), 0);
+    for (int rb = 0; rb < A.nrows; rb += 64 * W)
+      run_batch(resolve_rows<T>(A, A.rows, A.nrows, rb + lane * W + wave, gx0, gy0, gz0, B), 0);
   }
 
   if (COUNT) {
@@ -937,30 +977,11 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
     return;
   }
 
-  // add the stream partials of each i, one slot at a time: red[c][lane]
-  // (aliasing the j stage); particle u * nu + q is the sum over streams k of
-  // lane k * nu + q's slot u
-  T* red = reinterpret_cast<T*>(S.jb);
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    __syncthreads();
-    red[0 * 64 + lane] = ax[u];
-    red[1 * 64 + lane] = ay[u];
-    red[2 * 64 + lane] = az[u];
-    __syncthreads();
-    const int q = u * nu + lane;
-    if (lane >= nu || q >= ni) continue;
-    T sx = 0, sy = 0, sz = 0;
-#pragma unroll 2
-    for (int k = 0; k < ns; ++k) {
-      sx += red[0 * 64 + k * nu + lane];
-      sy += red[1 * 64 + k * nu + lane];
-      sz += red[2 * 64 + k * nu + lane];
-    }
+  // One i-particle's result from the complete sum over its partners.
+  auto emit = [&](int q, T sx, T sy, T sz) {
     const int fi = ibeg + q;
-    int run = 0;
-    while (run + 1 < GG && S.i_pre[run + 1] <= fi) ++run;
-    const int s = S.i_lo[run] + (fi - S.i_pre[run]);
+    const int run = find_run(i_pre, GG, fi);
+    const int s = i_lo[run] + (fi - i_pre[run]);
     const double m = (double)A.rec[s].w;
     const double ws = !SC ? A.wscale : (VJP ? A.wscale_vjp : A.wscale_rho);
     double gx = ws * (double)sx, gy = ws * (double)sy, gz = ws * (double)sz;
@@ -975,7 +996,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
       T4 o;
       o.x = (T)gx; o.y = (T)gy; o.z = (T)gz; o.w = T(0);
       A.acc_out[s] = o;
-      continue;
+      return;
     }
     const int64_t i = A.perm[s];
     if (A.force_fp32) {
@@ -989,17 +1010,56 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& S, int gx0,
       F[A.n + i] = m * gy;
       F[2 * A.n + i] = m * gz;
     }
+  };
+  // add the stream partials of each i, one slot at a time: lane st nu + il
+  // holds stream st of slot set il, and half of the streams are folded onto
+  // the other half until stream 0 holds the sum
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    T sx = ax[u], sy = ay[u], sz = az[u];
+    for (int m = ns; m > 1;) {
+      const int hm = (m + 1) >> 1, from = (lane + hm * nu) & 63;
+      const T tx = __shfl(sx, from, 64), ty = __shfl(sy, from, 64), tz = __shfl(sz, from, 64);
+      if (st + hm < m) {
+        sx += tx;
+        sy += ty;
+        sz += tz;
+      }
+      m = hm;
+    }
+    const int q = u * nu + lane;
+    if (lane >= nu || q >= ni) continue;
+    if constexpr (W == 1) {
+      emit(q, sx, sy, sz);
+    } else {
+      B0.wsum[wave][3 * q] = sx;
+      B0.wsum[wave][3 * q + 1] = sy;
+      B0.wsum[wave][3 * q + 2] = sz;
+    }
+  }
+  if constexpr (W > 1) {
+    __syncthreads();
+    if (wave == 0 && lane < ni) {
+      T sx = 0, sy = 0, sz = 0;
+#pragma unroll
+      for (int k = 0; k < W; ++k) {
+        sx += B0.wsum[k][3 * lane];
+        sy += B0.wsum[k][3 * lane + 1];
+        sz += B0.wsum[k][3 * lane + 2];
+      }
+      emit(lane, sx, sy, sz);
+    }
   }
 }
 
 // i-slots per lane: enough that ceil(ni / U) slot sets fit in the wave. The
 // one-sided sum rounds the slot sets up to a power of two NU.
-template <typename T, bool COUNT, bool UM, int TAB, bool VJP, bool HALF, typename SH>
+template <typename T, bool COUNT, bool UM, int TAB, bool VJP, bool HALF, int W, typename SH>
 __device__ __forceinline__ void pair_dispatch(const PairArgs<T>& A, SH& S,
                                               int gx0, int gy0, int gz0, int ibeg, int ni,
                                               int64_t g) {
 #define P3M_ITEM(U_, NU_) \
-  pair_item<T, U_, COUNT, UM, TAB, VJP, HALF, NU_>(A, S, gx0, gy0, gz0, ibeg, ni, g)
+  pair_item<T, U_, COUNT, UM, TAB, VJP, HALF, NU_, W>(A, S, gx0, gy0, gz0, ibeg, ni, g)
   if constexpr (!HALF) {
     if (ni == 1)
       P3M_ITEM(1, 0);
@@ -1039,11 +1099,12 @@ __device__ __forceinline__ void pair_dispatch(const PairArgs<T>& A, SH& S,
 #undef P3M_ITEM
 }
 
-template <typename T, bool COUNT, bool UM, int TAB, bool VJP = false, bool HALF = false>
-__global__ void __launch_bounds__(64, (kPairWaves<T, VJP>))
+template <typename T, bool COUNT, bool UM, int TAB, bool VJP = false, bool HALF = false,
+          int W = 1>
+__global__ void __launch_bounds__(64 * W, (kPairWaves<T, VJP>))
 k_pairs(PairArgs<T> A) {
-  __shared__ PairShared<T, VJP, HALF> S;
-  const int lane = threadIdx.x;
+  __shared__ PairShared<T, VJP, HALF, W> S;
+  const int lane = threadIdx.x & 63;
   // Items in group order, dealt round-robin over the XCDs by the hardware:
   // the eight XCDs then work on neighbouring groups at the same time, which
   // measured faster than giving each XCD its own slab of the box.
@@ -1058,10 +1119,11 @@ k_pairs(PairArgs<T> A) {
 
   if (!COUNT) {                        // split-factor table into LDS
     T* tab = &S.tab.c[0][0];
-    for (int e = lane; e < SplitTable<T>::kCoef * kTabStride; e += 64) tab[e] = A.split_tab[e];
+    for (int e = threadIdx.x; e < SplitTable<T>::kCoef * kTabStride; e += 64 * W)
+      tab[e] = A.split_tab[e];
   }
   // i side: the group's G*G z-runs
-  {
+  if (W == 1 || threadIdx.x < 64) {
     int cnt = 0;
     if (lane < GG) {
       int a = lane >> lgG, b = lane & (G - 1);
@@ -1077,20 +1139,27 @@ k_pairs(PairArgs<T> A) {
   __syncthreads();
   // wave-uniform counts (scalar registers, so the loops are scalar)
   const int ntot = __builtin_amdgcn_readfirstlane(S.i_pre[GG]);
-  const int ibeg = it.y * kChunk;
-  const int ni = min(kChunk, ntot - ibeg);
+  const int chunk = HALF ? kChunk : A.chunk;
+  const int ibeg = it.y * chunk;
+  const int ni = min(chunk, ntot - ibeg);
   // the one-sided sum for an item of a dense group, unless the partials
   // exceed the plan's capacity this call (then every pair from both sides,
   // as in a plan without partials); items of sparse groups from both sides
-  if (HALF && ntot > kDenseMin && *A.gtotal <= A.rcap)
-    pair_dispatch<T, COUNT, UM, TAB, VJP, true>(A, S, gx0, gy0, gz0, ibeg, ni, it.x);
-  else
-    pair_dispatch<T, COUNT, UM, TAB, VJP, false>(A, S, gx0, gy0, gz0, ibeg, ni, it.x);
+  if constexpr (HALF) {
+    if (ntot > kDenseMin && *A.gtotal <= A.rcap) {
+      pair_dispatch<T, COUNT, UM, TAB, VJP, true, 1>(A, S, gx0, gy0, gz0, ibeg, ni, it.x);
+      return;
+    }
+  }
+  pair_dispatch<T, COUNT, UM, TAB, VJP, false, W>(A, S, gx0, gy0, gz0, ibeg, ni, it.x);
 }
 
-// Grid of the pair kernel: the item bound rounded up to a multiple of kXcds.
-unsigned pair_grid(const p3m_plan* P) {
-  return (unsigned)((P->max_items + kXcds - 1) / kXcds * kXcds);
+// Grid of the pair kernel: the call's item bound (every group that can hold
+// a particle, and a further item per whole chunk) rounded up to a multiple of
+// kXcds.
+unsigned pair_grid(const p3m_plan* P, int64_t n) {
+  const int64_t items = std::min(P->ngroup, n) + n / P->chunk;
+  return (unsigned)((items + kXcds - 1) / kXcds * kXcds);
 }
 
 template <typename T>
@@ -1102,6 +1171,7 @@ PairArgs<T> make_args(p3m_plan* P, int64_t n) {
   A.start = W.start;
   A.items = W.items;
   A.n_items = W.goff + P->ngroup;
+  A.chunk = P->chunk;
   A.rows = W.rows;
   A.nrows = P->nrows;
   A.ng = P->ng;
@@ -1172,9 +1242,26 @@ double out_scale(const PairArgs<T>& A, int tab, bool vjp) {
 
 }  // namespace
 
+template <typename T, bool VJP, int W>
+hipError_t launch_two_sided(p3m_plan* P, const PairArgs<T>& A, bool uniform_mass, bool tab) {
+  const unsigned grid = pair_grid(P, A.n);
+  if (tab) {
+    if (uniform_mass)
+      k_pairs<T, false, true, 1, VJP, false, W><<<grid, 64 * W, 0, P->stream>>>(A);
+    else
+      k_pairs<T, false, false, 1, VJP, false, W><<<grid, 64 * W, 0, P->stream>>>(A);
+  } else {
+    if (uniform_mass)
+      k_pairs<T, false, true, 0, VJP, false, W><<<grid, 64 * W, 0, P->stream>>>(A);
+    else
+      k_pairs<T, false, false, 0, VJP, false, W><<<grid, 64 * W, 0, P->stream>>>(A);
+  }
+  return hipGetLastError();
+}
+
 template <typename T, bool VJP>
 hipError_t launch_pair_kernel(p3m_plan* P, const PairArgs<T>& A, bool uniform_mass, bool half) {
-  const unsigned grid = pair_grid(P);
+  const unsigned grid = pair_grid(P, A.n);
   const bool tab = (sizeof(T) == 4 ? P->tab_var : P->tab64_var) == 1;
   // table over the softened distance (1) or over r (0)
   if (half) {
@@ -1191,25 +1278,19 @@ hipError_t launch_pair_kernel(p3m_plan* P, const PairArgs<T>& A, bool uniform_ma
     }
     return hipGetLastError();
   }
-  if (tab) {
-    if (uniform_mass)
-      k_pairs<T, false, true, 1, VJP><<<grid, 64, 0, P->stream>>>(A);
-    else
-      k_pairs<T, false, false, 1, VJP><<<grid, 64, 0, P->stream>>>(A);
-  } else {
-    if (uniform_mass)
-      k_pairs<T, false, true, 0, VJP><<<grid, 64, 0, P->stream>>>(A);
-    else
-      k_pairs<T, false, false, 0, VJP><<<grid, 64, 0, P->stream>>>(A);
+  switch (P->item_waves) {
+    case 2: return launch_two_sided<T, VJP, 2>(P, A, uniform_mass, tab);
+    case 4: return launch_two_sided<T, VJP, 4>(P, A, uniform_mass, tab);
+    case 8: return launch_two_sided<T, VJP, 8>(P, A, uniform_mass, tab);
+    default: return launch_two_sided<T, VJP, 1>(P, A, uniform_mass, tab);
   }
-  return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_pairs(p3m_plan* P, int64_t n, bool add_pm, void* force_out, int force_fp32,
                         bool uniform_mass, void* acc_out) {
   PairArgs<T> A = make_args<T>(P, n);
-  if (P->rcap > 0 && !add_pm) {
+  if (P->one_sided && !add_pm) {
     // one-sided sum: the sorted action into ws.acc_pm; launch_pair_gather
     // then adds the reactions and writes the result
     A.acc_out = (typename Vec<T>::v4*)P->ws.acc_pm;
@@ -1227,7 +1308,7 @@ hipError_t launch_pairs_vjp(p3m_plan* P, int64_t n, bool add_pm, double* pos_bar
                             bool uniform_mass, void* acc_out) {
   PairArgs<T> A = make_args<T>(P, n);
   A.lam = (const typename Vec<T>::v4*)P->ws.lam;
-  if (P->rcap > 0 && !add_pm) {
+  if (P->one_sided && !add_pm) {
     A.acc_out = (typename Vec<T>::v4*)P->ws.acc_pm;
     return launch_pair_kernel<T, true>(P, A, uniform_mass, true);
   }
@@ -1253,19 +1334,30 @@ hipError_t launch_pair_count(p3m_plan* P, int64_t n, int64_t* count_out) {
   A.counter = (unsigned long long*)count_out;
   hipError_t e = launch_fill_i32((int32_t*)count_out, 2, 0, P->stream);
   if (e != hipSuccess) return e;
-  k_pairs<T, true, true, 0><<<pair_grid(P), 64, 0, P->stream>>>(A);
+  k_pairs<T, true, true, 0><<<pair_grid(P, n), 64, 0, P->stream>>>(A);
   return hipGetLastError();
 }
 
+// The kernels of each precision and direction are compiled by a translation
+// unit of their own (pair_f64.hip, pair_vjp_f32.hip and pair_vjp_f64.hip
+// include this file), so that they build side by side.
+#ifndef P3M_PAIR_PART
+#define P3M_PAIR_PART 0
+#endif
+#if P3M_PAIR_PART == 0
 template hipError_t launch_pairs<float>(p3m_plan*, int64_t, bool, void*, int, bool, void*);
-template hipError_t launch_pairs<double>(p3m_plan*, int64_t, bool, void*, int, bool, void*);
-template hipError_t launch_pairs_vjp<float>(p3m_plan*, int64_t, bool, double*, bool, void*);
-template hipError_t launch_pairs_vjp<double>(p3m_plan*, int64_t, bool, double*, bool, void*);
+template hipError_t launch_pair_count<float>(p3m_plan*, int64_t, int64_t*);
 template hipError_t launch_pair_gather<float>(p3m_plan*, int64_t, bool, bool, void*, void*,
                                                int, const void*);
 template hipError_t launch_pair_gather<double>(p3m_plan*, int64_t, bool, bool, void*, void*,
                                                 int, const void*);
-template hipError_t launch_pair_count<float>(p3m_plan*, int64_t, int64_t*);
+#elif P3M_PAIR_PART == 1
+template hipError_t launch_pairs<double>(p3m_plan*, int64_t, bool, void*, int, bool, void*);
 template hipError_t launch_pair_count<double>(p3m_plan*, int64_t, int64_t*);
+#elif P3M_PAIR_PART == 2
+template hipError_t launch_pairs_vjp<float>(p3m_plan*, int64_t, bool, double*, bool, void*);
+#else
+template hipError_t launch_pairs_vjp<double>(p3m_plan*, int64_t, bool, double*, bool, void*);
+#endif
 
 }  // namespace p3m
