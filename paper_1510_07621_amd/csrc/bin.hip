@@ -6,10 +6,18 @@
 // one contiguous run of particles after sorting. Steps:
 //   1. keys + histogram: cell of each particle; atomic count per cell, whose
 //      return value is the particle's rank inside the cell;
-//   2. exclusive scan of the counts -> first slot of every cell;
-//   3. scatter + pack: each particle goes to slot start[c] + rank as a record
-//      of its offset from the cell's lower corner (in the path's precision)
-//      and its mass, with its input index (perm) and cell (skey).
+//   2. exclusive scan of the counts inside tiles of 2048 cells, and the tiles'
+//      totals;
+//   3. one launch of three kinds of blocks, each adding the totals of the
+//      tiles before a cell's own to its place in the tile: the first slot of
+//      every cell (start); scatter + pack, each particle to slot start[c] +
+//      rank as a record of its offset from the cell's lower corner (in the
+//      path's precision) and its mass, with its input index (perm) and cell
+//      (skey); and the pair loop's work items.
+// Small sets wait for launches, not for these kernels' work: about 5 us a
+// launch from end to end, so that eight kernels in line (scan of the tiles,
+// of their totals, add, scatter, three for the items) cost a 4096-particle
+// force call 40 us.
 // The order inside a cell follows the atomic ranks, so it can differ between
 // runs; every later step is a sum, so only rounding depends on it.
 #include "p3m_internal.h"
@@ -21,6 +29,7 @@ constexpr int kThreads = 256;
 constexpr int kScanItems = 8;                       // per thread
 constexpr int kScanTile = kThreads * kScanItems;    // per block
 static_assert(kScanItems == 8, "k_scan_tiles moves a thread's values as two int4");
+constexpr int kFuseTiles = 1024;    // tiles whose totals each block of the last pass scans
 
 __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -72,30 +81,7 @@ k_bin_count(int64_t n, const double* __restrict__ pos, int ng, int lg, double in
   if (valid) rank[i] = base + (lane - start);
 }
 
-template <typename T>
-__global__ void k_scatter(int64_t n, const double* __restrict__ pos,
-                          const double* __restrict__ mass, double mass_scalar, int ng,
-                          int lg, double h, const int32_t* __restrict__ key,
-                          const int32_t* __restrict__ rank,
-                          const int32_t* __restrict__ start, int32_t* __restrict__ perm,
-                          int32_t* __restrict__ skey, typename Vec<T>::v4* __restrict__ rec) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int c = key[i];
-  int dst = start[c] + rank[i];
-  int mask = ng - 1;
-  int cz = c & mask, cy = (c >> lg) & mask, cx = c >> (2 * lg);
-  typename Vec<T>::v4 r;
-  r.x = (T)(pos[i] - cx * h);
-  r.y = (T)(pos[n + i] - cy * h);
-  r.z = (T)(pos[2 * n + i] - cz * h);
-  r.w = (T)(mass ? mass[i] : mass_scalar);
-  rec[dst] = r;
-  perm[dst] = (int32_t)i;
-  skey[dst] = c;
-}
-
-// ---- exclusive scan of int32 (three kernels: tiles, tile sums, add) ----
+// ---- exclusive scan of the cell counts: tiles, then the tiles' totals ----
 
 __device__ __forceinline__ int wave_inclusive(int v) {
   const int lane = threadIdx.x & 63;
@@ -124,9 +110,9 @@ __device__ __forceinline__ int block_exclusive(int v, int* __restrict__ wsum, in
   return base + inc - v;
 }
 
-// ZERO: the input is cleared as it is read (the cell counts, so that the
-// next binning starts from zero without a fill pass).
-template <bool ZERO>
+// Each tile's exclusive scan and its total; the counts are cleared as they
+// are read, so that the next binning starts from zero without a fill pass.
+// (Values move as two int4: in and out are 16-byte aligned allocations.)
 __global__ void __launch_bounds__(kThreads)
 k_scan_tiles(int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t len,
              int32_t* __restrict__ tile_sum) {
@@ -141,18 +127,14 @@ k_scan_tiles(int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t len,
     const int4 b = reinterpret_cast<const int4*>(in + base)[1];
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
     v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    if (ZERO) {
-      reinterpret_cast<int4*>(in + base)[0] = int4{0, 0, 0, 0};
-      reinterpret_cast<int4*>(in + base)[1] = int4{0, 0, 0, 0};
-    }
+    reinterpret_cast<int4*>(in + base)[0] = int4{0, 0, 0, 0};
+    reinterpret_cast<int4*>(in + base)[1] = int4{0, 0, 0, 0};
   } else {
 #pragma unroll
     for (int k = 0; k < kScanItems; ++k) v[k] = (base + k < len) ? in[base + k] : 0;
-    if (ZERO) {
 #pragma unroll
-      for (int k = 0; k < kScanItems; ++k)
-        if (base + k < len) in[base + k] = 0;
-    }
+    for (int k = 0; k < kScanItems; ++k)
+      if (base + k < len) in[base + k] = 0;
   }
   int local = 0;
 #pragma unroll
@@ -176,10 +158,9 @@ k_scan_tiles(int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t len,
   if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
 }
 
-// Single block: exclusive scan of the tile sums in place; writes the grand
-// total to *grand.
+// Single block: exclusive scan of the tile sums in place.
 __global__ void __launch_bounds__(1024)
-k_scan_sums(int32_t* __restrict__ sums, int nt, int32_t* __restrict__ grand) {
+k_scan_sums(int32_t* __restrict__ sums, int nt) {
   __shared__ int wsum[1024 / 64];
   int carry = 0;
   for (int b = 0; b < nt; b += blockDim.x) {
@@ -190,129 +171,165 @@ k_scan_sums(int32_t* __restrict__ sums, int nt, int32_t* __restrict__ grand) {
     if (i < nt) sums[i] = carry + ex;
     carry += total;
   }
-  if (threadIdx.x == 0) *grand = carry;
 }
 
-// Whole tiles as int4 (consecutive threads, consecutive 16 bytes), the
-// ragged last tile one value at a time.
+// ---- the last pass: cell starts, sorted records, work items ----
+
+// What k_bin_finish works on. lstart: each cell's slot within its tile;
+// tile: the tiles' totals (NSUM > 0) or their exclusive scan (NSUM 0).
+template <typename T>
+struct FinishArgs {
+  int64_t n;
+  const double* __restrict__ pos;
+  const double* __restrict__ mass;
+  double mass_scalar;
+  int ng, lg;
+  double h;
+  const int32_t* __restrict__ key;
+  const int32_t* __restrict__ rank;
+  const int32_t* __restrict__ lstart;
+  const int32_t* __restrict__ tile;
+  int nt;
+  int64_t ncell;
+  int32_t* __restrict__ start;
+  int32_t* __restrict__ perm;
+  int32_t* __restrict__ skey;
+  typename Vec<T>::v4* __restrict__ rec;
+  int scatter_blocks, start_blocks;     // then the blocks of the work items
+  int G, lgG;
+  int64_t ngroup;
+  int chunk;
+  int2* __restrict__ items;
+};
+
+// Where the items of the groups from g on begin: g places and one for every
+// whole chunk of the particles in the groups before g (x slabs, then y rows
+// of the slab, then z; group g's own slab and row column by column).
+template <typename T, typename F>
+__device__ __forceinline__ int64_t items_before(const FinishArgs<T>& A, const F& first,
+                                                int64_t g) {
+  if (g >= A.ngroup) return A.ngroup + A.n / A.chunk;
+  const int lgd = A.lg - A.lgG, md = (1 << lgd) - 1;
+  const int gz = (int)(g & md), gy = (int)((g >> lgd) & md), gx = (int)(g >> (2 * lgd));
+  const auto cell = [&](int x, int y, int z) { return (((x << A.lg) | y) << A.lg) | z; };
+  int64_t before = first(cell(gx * A.G, 0, 0));
+  for (int x = gx * A.G; x < (gx + 1) * A.G; ++x) {
+    before += first(cell(x, gy * A.G, 0)) - first(cell(x, 0, 0));
+    if (gz)
+      for (int y = gy * A.G; y < (gy + 1) * A.G; ++y)
+        before += first(cell(x, y, gz * A.G)) - first(cell(x, y, 0));
+  }
+  return g + before / A.chunk;
+}
+
+// NSUM > 0: each block scans the tiles' totals itself, NSUM a thread (one
+// launch less; up to kFuseTiles tiles, 128^3 cells, where a block's share is
+// 4 KB from the L2). 0: scanned by k_scan_sums.
+template <typename T, int NSUM>
 __global__ void __launch_bounds__(kThreads)
-k_scan_add(int32_t* __restrict__ out, int64_t len, const int32_t* __restrict__ tile_off) {
-  int64_t base = (int64_t)blockIdx.x * kScanTile;
-  int add = tile_off[blockIdx.x];
-  if (base + kScanTile <= len) {
-    int4* o = reinterpret_cast<int4*>(out + base);
-    for (int k = threadIdx.x; k < kScanTile / 4; k += kThreads) {
-      int4 q = o[k];
-      q.x += add; q.y += add; q.z += add; q.w += add;
-      o[k] = q;
+k_bin_finish(FinishArgs<T> A) {
+  __shared__ int off[NSUM ? NSUM * kThreads : 1];
+  __shared__ int wsum[kThreads / 64];
+  if constexpr (NSUM > 0) {
+    int v[NSUM], local = 0, total;
+#pragma unroll
+    for (int k = 0; k < NSUM; ++k) {
+      const int t = (int)threadIdx.x * NSUM + k;
+      v[k] = t < A.nt ? A.tile[t] : 0;
+      local += v[k];
     }
+    int run = block_exclusive(local, wsum, total);
+#pragma unroll
+    for (int k = 0; k < NSUM; ++k) {
+      off[threadIdx.x * NSUM + k] = run;
+      run += v[k];
+    }
+    __syncthreads();
+  }
+  const auto offset = [&](int t) { return NSUM ? off[t] : A.tile[t]; };
+  const auto first = [&](int64_t c) {       // first slot of cell c; of c = ncell: n
+    return c < A.ncell ? A.lstart[c] + offset((int)(c / kScanTile)) : (int)A.n;
+  };
+  int b = blockIdx.x;
+  if (b < A.scatter_blocks) {
+    const int64_t n = A.n, i = (int64_t)b * kThreads + threadIdx.x;
+    if (i >= n) return;
+    const int c = A.key[i];
+    const int dst = first(c) + A.rank[i];
+    const int mask = A.ng - 1;
+    const int cz = c & mask, cy = (c >> A.lg) & mask, cx = c >> (2 * A.lg);
+    typename Vec<T>::v4 r;
+    r.x = (T)(A.pos[i] - cx * A.h);
+    r.y = (T)(A.pos[n + i] - cy * A.h);
+    r.z = (T)(A.pos[2 * n + i] - cz * A.h);
+    r.w = (T)(A.mass ? A.mass[i] : A.mass_scalar);
+    A.rec[dst] = r;
+    A.perm[dst] = (int32_t)i;
+    A.skey[dst] = c;
     return;
   }
-  for (int k = threadIdx.x; k < kScanTile; k += kThreads) {
-    int64_t i = base + k;
-    if (i < len) out[i] += add;
-  }
-}
-
-// ---- pair-loop work list ----
-
-// Chunks of one i-group: its particles (G x G z-runs of G cells) over the chunk.
-__device__ __forceinline__ int group_chunks(const int32_t* __restrict__ start, int lg, int G,
-                                            int lgG, int64_t g, int chunk) {
-  const int lgd = lg - lgG, md = (1 << lgd) - 1;
-  int gz = (int)(g & md), gy = (int)((g >> lgd) & md), gx = (int)(g >> (2 * lgd));
-  int cnt = 0;
-  for (int a = 0; a < G; ++a)
-    for (int b = 0; b < G; ++b) {
-      int c0 = ((((gx * G + a) << lg) | (gy * G + b)) << lg) | (gz * G);
-      cnt += start[c0 + G] - start[c0];
+  b -= A.scatter_blocks;
+  if (b < A.start_blocks) {
+    // one tile: whole tiles as int4 (consecutive threads, consecutive 16
+    // bytes), the ragged last tile one value at a time
+    const int64_t base = (int64_t)b * kScanTile;
+    const int add = offset(b);
+    if (base + kScanTile <= A.ncell) {
+      const int4* in = reinterpret_cast<const int4*>(A.lstart + base);
+      int4* out = reinterpret_cast<int4*>(A.start + base);
+      for (int k = threadIdx.x; k < kScanTile / 4; k += kThreads) {
+        int4 q = in[k];
+        q.x += add; q.y += add; q.z += add; q.w += add;
+        out[k] = q;
+      }
+    } else {
+      for (int64_t c = base + threadIdx.x; c < A.ncell; c += kThreads)
+        A.start[c] = A.lstart[c] + add;
     }
-  return (cnt + chunk - 1) / chunk;
-}
-
-// Work list, pass 1: chunk counts of a tile of kThreads groups (one per
-// thread), their exclusive scan within the tile (goff) and the tile total.
-__global__ void __launch_bounds__(kThreads)
-k_items_tiles(const int32_t* __restrict__ start, int lg, int G, int lgG, int64_t ngroup, int chunk,
-              int32_t* __restrict__ gchunk, int32_t* __restrict__ goff,
-              int32_t* __restrict__ tile_sum) {
-  __shared__ int wsum[kThreads / 64];
-  const int64_t g = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const int v = g < ngroup ? group_chunks(start, lg, G, lgG, g, chunk) : 0;
-  int total;
-  const int ex = block_exclusive(v, wsum, total);
-  if (g < ngroup) {
-    gchunk[g] = v;
-    goff[g] = ex;
+    if (b == 0 && threadIdx.x == 0) A.start[A.ncell] = (int)A.n;
+    return;
   }
-  if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
-}
-
-// Pass 3 (after the tile sums are scanned): each group's items at its offset.
-__global__ void __launch_bounds__(kThreads)
-k_emit_items(const int32_t* __restrict__ gchunk, const int32_t* __restrict__ goff,
-             const int32_t* __restrict__ tile_off, int64_t ngroup, int2* __restrict__ items) {
-  int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= ngroup) return;
-  int nc = gchunk[g], o = goff[g] + tile_off[g / kThreads];
-  for (int c = 0; c < nc; ++c) items[o + c] = make_int2((int)g, c);
+  b -= A.start_blocks;
+  // One group a thread: its chunks (the particles of its G x G z-runs over the
+  // chunk), in group order. All groups before g together have at most
+  // g + (their particles) / chunk items, so the block's list begins there (no
+  // block needs another's counts), and the places up to the next block's
+  // beginning are marked empty. (Appended by atomics, the blocks' order was
+  // free and neighbouring groups no longer ran together: 128^3 lattice FP32
+  // 2.39 -> 2.46 ms.)
+  const int64_t g0 = (int64_t)b * kThreads;
+  const int64_t base = items_before(A, first, g0);
+  const int64_t next = items_before(A, first, min(g0 + kThreads, A.ngroup));
+  const int64_t g = g0 + threadIdx.x;
+  int nc = 0, total;
+  if (g < A.ngroup) {
+    const int lgd = A.lg - A.lgG, md = (1 << lgd) - 1;
+    const int gz = (int)(g & md), gy = (int)((g >> lgd) & md), gx = (int)(g >> (2 * lgd));
+    int cnt = 0;
+    for (int x = 0; x < A.G; ++x)
+      for (int y = 0; y < A.G; ++y) {
+        const int c0 = ((((gx * A.G + x) << A.lg) | (gy * A.G + y)) << A.lg) | (gz * A.G);
+        cnt += first(c0 + A.G) - first(c0);
+      }
+    nc = (cnt + A.chunk - 1) / A.chunk;
+  }
+  const int64_t at = base + block_exclusive(nc, wsum, total);
+  for (int c = 0; c < nc; ++c) A.items[at + c] = make_int2((int)g, c);
+  for (int64_t i = base + total + threadIdx.x; i < next; i += kThreads)
+    A.items[i] = make_int2(-1, 0);
 }
 
 inline unsigned blocks_for(int64_t n, int t) { return (unsigned)((n + t - 1) / t); }
 
 }  // namespace
 
-int scan_tmp_size(int64_t len) { return (int)((len + kScanTile - 1) / kScanTile) + 1; }
-int items_tmp_size(int64_t ngroup) { return (int)((ngroup + kThreads - 1) / kThreads) + 1; }
+int scan_tiles(int64_t ncell) { return (int)((ncell + kScanTile - 1) / kScanTile); }
 
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   int64_t b = (n + kThreads - 1) / kThreads;
   unsigned blocks = (unsigned)(b < 65536 ? b : 65536);
   k_fill_i32<<<blocks, kThreads, 0, s>>>(p, n, v);
-  return hipGetLastError();
-}
-
-// out[0..len) = exclusive scan of in[0..len); out[len] = total; with
-// zero_in, in[0..len) is cleared as it is read. tmp needs scan_tmp_size(len)
-// entries; in and out must be 16-byte aligned (device allocations are).
-hipError_t launch_scan(int32_t* in, int32_t* out, int64_t len, int32_t* tmp, hipStream_t s,
-                       bool zero_in) {
-  if ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15)
-    return hipErrorInvalidValue;
-  int nt = (int)((len + kScanTile - 1) / kScanTile);
-  if (nt == 0) return launch_fill_i32(out, 1, 0, s);
-  if (zero_in)
-    k_scan_tiles<true><<<nt, kThreads, 0, s>>>(in, out, len, tmp);
-  else
-    k_scan_tiles<false><<<nt, kThreads, 0, s>>>(in, out, len, tmp);
-  k_scan_sums<<<1, 1024, 0, s>>>(tmp, nt, out + len);
-  k_scan_add<<<nt, kThreads, 0, s>>>(out, len, tmp);
-  return hipGetLastError();
-}
-
-hipError_t launch_bin(p3m_plan* P, int64_t n, const double* pos, const double* mass,
-                      double mass_scalar) {
-  Workspace& W = P->ws;
-  hipStream_t s = P->stream;
-  hipError_t e;
-  // The counts start at zero: cleared by the previous binning's scan, or
-  // here when that binning did not get as far (a failed launch)
-  if (P->count_dirty && (e = launch_fill_i32(W.count, P->ncell, 0, s)) != hipSuccess) return e;
-  P->count_dirty = 1;
-  k_bin_count<<<blocks_for(n, kThreads), kThreads, 0, s>>>(n, pos, P->ng, P->lg, 1.0 / P->h,
-                                                           W.key, W.rank, W.count);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_scan(W.count, W.start, P->ncell, W.scan_tmp, s, true)) != hipSuccess) return e;
-  P->count_dirty = 0;
-  if (P->prm.precision == P3M_FP32)
-    k_scatter<float><<<blocks_for(n, kThreads), kThreads, 0, s>>>(
-        n, pos, mass, mass_scalar, P->ng, P->lg, P->h, W.key, W.rank, W.start, W.perm,
-        W.skey, (float4*)W.rec);
-  else
-    k_scatter<double><<<blocks_for(n, kThreads), kThreads, 0, s>>>(
-        n, pos, mass, mass_scalar, P->ng, P->lg, P->h, W.key, W.rank, W.start, W.perm,
-        W.skey, (double4*)W.rec);
   return hipGetLastError();
 }
 
@@ -353,25 +370,72 @@ static void pair_split(p3m_plan* P, int64_t n) {
   }
 }
 
-hipError_t launch_items(p3m_plan* P, int64_t n, bool whole) {
+template <typename T>
+static hipError_t launch_finish(p3m_plan* P, int64_t n, const double* pos, const double* mass,
+                                double mass_scalar, Items items) {
   Workspace& W = P->ws;
+  FinishArgs<T> A{};
+  A.n = n;
+  A.pos = pos;
+  A.mass = mass;
+  A.mass_scalar = mass_scalar;
+  A.ng = P->ng;
+  A.lg = P->lg;
+  A.h = P->h;
+  A.key = W.key;
+  A.rank = W.rank;
+  A.lstart = W.lstart;
+  A.tile = W.scan_tmp;
+  A.nt = scan_tiles(P->ncell);
+  A.ncell = P->ncell;
+  A.start = W.start;
+  A.perm = W.perm;
+  A.skey = W.skey;
+  A.rec = (typename Vec<T>::v4*)W.rec;
+  A.scatter_blocks = (int)blocks_for(n, kThreads);
+  A.start_blocks = A.nt;
+  A.G = P->G;
+  A.lgG = P->lgG;
+  A.ngroup = P->ngroup;
+  A.chunk = P->chunk;
+  A.items = W.items;
+  const unsigned blocks = (unsigned)(A.scatter_blocks + A.start_blocks) +
+                          (items == Items::kNone ? 0 : blocks_for(P->ngroup, kThreads));
+  if (A.nt <= kThreads)
+    k_bin_finish<T, 1><<<blocks, kThreads, 0, P->stream>>>(A);
+  else if (A.nt <= kFuseTiles)
+    k_bin_finish<T, kFuseTiles / kThreads><<<blocks, kThreads, 0, P->stream>>>(A);
+  else
+    k_bin_finish<T, 0><<<blocks, kThreads, 0, P->stream>>>(A);
+  return hipGetLastError();
+}
+
+hipError_t launch_bin(p3m_plan* P, int64_t n, const double* pos, const double* mass,
+                      double mass_scalar, Items items) {
+  Workspace& W = P->ws;
+  hipStream_t s = P->stream;
+  hipError_t e;
   P->chunk = kChunk;
   P->item_waves = 1;
-  if (!whole) pair_split(P, n);
-  hipStream_t s = P->stream;
-  // chunk counts + tile scans, scan of the tile sums (total to goff[ngroup]),
-  // then the items at tile offset + offset within the tile
-  const int nt = (int)((P->ngroup + kThreads - 1) / kThreads);
-  k_items_tiles<<<nt, kThreads, 0, s>>>(W.start, P->lg, P->G, P->lgG, P->ngroup, P->chunk, W.gchunk,
-                                        W.goff, W.scan_tmp);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  k_scan_sums<<<1, 1024, 0, s>>>(W.scan_tmp, nt, W.goff + P->ngroup);
+  if (items == Items::kCut) pair_split(P, n);
+  // The counts start at zero: cleared by the previous binning's scan, or
+  // here when that binning did not get as far (a failed launch)
+  if (P->count_dirty && (e = launch_fill_i32(W.count, P->ncell, 0, s)) != hipSuccess) return e;
+  P->count_dirty = 1;
+  k_bin_count<<<blocks_for(n, kThreads), kThreads, 0, s>>>(n, pos, P->ng, P->lg, 1.0 / P->h,
+                                                           W.key, W.rank, W.count);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_emit_items<<<blocks_for(P->ngroup, kThreads), kThreads, 0, s>>>(W.gchunk, W.goff,
-                                                                    W.scan_tmp, P->ngroup,
-                                                                    W.items);
-  return hipGetLastError();
+  const int nt = scan_tiles(P->ncell);
+  k_scan_tiles<<<nt, kThreads, 0, s>>>(W.count, W.lstart, P->ncell, W.scan_tmp);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  P->count_dirty = 0;
+  if (nt > kFuseTiles) {
+    k_scan_sums<<<1, 1024, 0, s>>>(W.scan_tmp, nt);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  return P->prm.precision == P3M_FP32
+             ? launch_finish<float>(P, n, pos, mass, mass_scalar, items)
+             : launch_finish<double>(P, n, pos, mass, mass_scalar, items);
 }
 
 }  // namespace p3m

@@ -58,9 +58,8 @@ size_t carve(p3m_plan* P, unsigned char* base, int64_t n) {
   W.skey = (int32_t*)take(sizeof(int32_t) * nn);
   W.count = (int32_t*)take(sizeof(int32_t) * (P->ncell + 1));
   W.start = (int32_t*)take(sizeof(int32_t) * (P->ncell + 1));
-  W.scan_tmp = (int32_t*)take(sizeof(int32_t) * P->scan_tmp_len);
-  W.gchunk = (int32_t*)take(sizeof(int32_t) * (P->ngroup + 1));
-  W.goff = (int32_t*)take(sizeof(int32_t) * (P->ngroup + 1));
+  W.scan_tmp = (int32_t*)take(sizeof(int32_t) * p3m::scan_tiles(P->ncell));
+  W.lstart = (int32_t*)take(sizeof(int32_t) * P->ncell);
   W.items = (int2*)take(sizeof(int2) * P->max_items);
   W.rows = (int4*)take(sizeof(int4) * P->nrows);
   W.rec = take(4 * real * nn);
@@ -108,8 +107,8 @@ extern "C" int pp_force_noalloc(const p3m_params* params, int64_t n, const doubl
   P.device = dev;
   carve(&P, base, n);
   if ((e = p3m::plan_upload_tables(&P, g_rows)) != hipSuccess) return status_of(e);
-  if ((e = p3m::launch_bin(&P, n, pos, mass, mass_scalar)) != hipSuccess) return status_of(e);
-  if ((e = p3m::launch_items(&P, n, false)) != hipSuccess) return status_of(e);
+  if ((e = p3m::launch_bin(&P, n, pos, mass, mass_scalar, p3m::Items::kCut)) != hipSuccess)
+    return status_of(e);
   e = params->precision == P3M_FP32
           ? p3m::launch_pairs<float>(&P, n, false, force, force_fp32 ? 1 : 0, mass == nullptr)
           : p3m::launch_pairs<double>(&P, n, false, force, force_fp32 ? 1 : 0, mass == nullptr);

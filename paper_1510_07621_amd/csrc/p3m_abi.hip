@@ -42,7 +42,7 @@ T* dev_alloc(size_t count, hipError_t& err) {
 void free_workspace(p3m_plan* P) {
   Workspace& W = P->ws;
   void* ptrs[] = {W.key,  W.rank,   W.count,  W.start, W.perm,  W.skey,    W.scan_tmp,
-                  W.gchunk, W.goff, W.items,  W.rows,  W.rec,   W.acc_pm,  W.grid,
+                  W.lstart, W.items,  W.rows,  W.rec,   W.acc_pm,  W.grid,
                   W.spec, W.twiddle, W.gtab,  W.counter, W.split_tab, W.split_tab64, W.lam,
                   W.grid2, W.lam_grid, W.power_acc, W.ewald_tab, W.ewald_zpair,
                   W.segrows, W.prows, W.pbrows, W.pboff, W.rowoff, W.gipre, W.gntot,
@@ -127,8 +127,8 @@ hipError_t run_force(p3m_plan* P, int64_t n, const double* pos, const double* ma
   P->one_sided = half;
   {
     StageTimer t(P, P3M_STAGE_BIN);
-    if ((e = launch_bin(P, n, pos, mass, ms)) != hipSuccess) return e;
-    if (part != Part::kPM && (e = launch_items(P, n, half)) != hipSuccess) return e;
+    const Items items = part == Part::kPM ? Items::kNone : half ? Items::kWhole : Items::kCut;
+    if ((e = launch_bin(P, n, pos, mass, ms, items)) != hipSuccess) return e;
     if (half && (e = launch_react_prepass(P)) != hipSuccess) return e;
   }
   if (part == Part::kP3M) {
@@ -233,8 +233,8 @@ hipError_t run_vjp(p3m_plan* P, int64_t n, const double* pos, const double* mass
   P->one_sided = half;
   {
     StageTimer t(P, P3M_STAGE_BIN);
-    if ((e = launch_bin(P, n, pos, mass, ms)) != hipSuccess) return e;
-    if (part != Part::kPM && (e = launch_items(P, n, half)) != hipSuccess) return e;
+    const Items items = part == Part::kPM ? Items::kNone : half ? Items::kWhole : Items::kCut;
+    if ((e = launch_bin(P, n, pos, mass, ms, items)) != hipSuccess) return e;
     if (half && (e = launch_react_prepass(P)) != hipSuccess) return e;
     if ((e = launch_lambda_sort<T>(P, n, fbar)) != hipSuccess) return e;
   }
@@ -611,7 +611,6 @@ int plan_geometry(const p3m_params& q, int64_t n_max, p3m_plan* P) {
   P->nseg = segment_rows(P->G, r_c / h, nullptr, 0, &P->npos);
   if (P->nseg < 0) return P->nseg;
   P->max_items = P->ngroup + n_max / kMinChunk;
-  P->scan_tmp_len = std::max(scan_tmp_size(P->ncell), items_tmp_size(P->ngroup));
   return P3M_OK;
 }
 
@@ -785,9 +784,8 @@ int p3m_plan_create(const p3m_params* prm, int64_t n_max, void* hip_stream, p3m_
   W.start = dev_alloc<int32_t>(P->ncell + 1, err);
   W.perm = dev_alloc<int32_t>(nn, err);
   W.skey = dev_alloc<int32_t>(nn, err);
-  W.scan_tmp = dev_alloc<int32_t>(P->scan_tmp_len, err);
-  W.gchunk = dev_alloc<int32_t>(P->ngroup + 1, err);
-  W.goff = dev_alloc<int32_t>(P->ngroup + 1, err);
+  W.scan_tmp = dev_alloc<int32_t>(scan_tiles(P->ncell), err);
+  W.lstart = dev_alloc<int32_t>(P->ncell, err);
   W.items = dev_alloc<int2>(P->max_items, err);
   W.rows = dev_alloc<int4>(P->nrows, err);
   W.rec = dev_alloc<unsigned char>(nn * 4 * real, err);
@@ -943,7 +941,8 @@ int p3m_power_spectrum(p3m_plan* P, int64_t n, const double* pos, const double* 
   hipError_t e;
   {
     StageTimer t(P, P3M_STAGE_BIN);
-    if ((e = launch_bin(P, n, pos, mass, mass_scalar)) != hipSuccess) return status_of(e);
+    if ((e = launch_bin(P, n, pos, mass, mass_scalar, Items::kNone)) != hipSuccess)
+      return status_of(e);
   }
   const bool f32 = P->prm.precision == P3M_FP32;
   {
@@ -971,7 +970,7 @@ int pp_ewald_force(p3m_plan* P, int64_t n, const double* pos, const double* mass
     return P3M_EINVAL;
   P->timing_slot = -1;
   // the binning's permutation orders the i-particles by cell (table locality)
-  hipError_t e = launch_bin(P, n, pos, mass, mass_scalar);
+  hipError_t e = launch_bin(P, n, pos, mass, mass_scalar, Items::kNone);
   if (e != hipSuccess) return status_of(e);
   return status_of(launch_pp_ewald(P, n, pos, mass, mass_scalar, P->ws.perm, force,
                                    force_fp32 ? 1 : 0));
@@ -993,8 +992,8 @@ int p3m_pair_count(p3m_plan* P, int64_t n, const double* pos, int64_t* count_out
   hipError_t e;
   if (n == 0) return status_of(launch_fill_i32((int32_t*)count_out, 2, 0, P->stream));
   P->timing_slot = -1;
-  if ((e = launch_bin(P, n, pos, nullptr, 1.0)) != hipSuccess) return status_of(e);
-  if ((e = launch_items(P, n, true)) != hipSuccess) return status_of(e);
+  if ((e = launch_bin(P, n, pos, nullptr, 1.0, Items::kWhole)) != hipSuccess)
+    return status_of(e);
   e = P->prm.precision == P3M_FP32 ? launch_pair_count<float>(P, n, count_out)
                                    : launch_pair_count<double>(P, n, count_out);
   return status_of(e);

@@ -73,10 +73,10 @@ struct Workspace {
   int32_t* start = nullptr;     // [ncell+1] first sorted slot of each cell; start[ncell] = n
   int32_t* perm = nullptr;      // [n_max]   sorted slot -> input index
   int32_t* skey = nullptr;      // [n_max]   cell index per sorted slot
-  int32_t* scan_tmp = nullptr;  // block sums of the scans
-  int32_t* gchunk = nullptr;    // [ngroup+1] 64-particle chunks per i-group
-  int32_t* goff = nullptr;      // [ngroup+1] exclusive scan of gchunk; goff[ngroup] = items
-  int2* items = nullptr;        // [max_items] (group, chunk) work items of the pair loop
+  int32_t* scan_tmp = nullptr;  // [scan_tiles] totals of the scan's tiles
+  int32_t* lstart = nullptr;    // [ncell]   start within the scan's tiles
+  int2* items = nullptr;        // [max_items] (group, chunk) work items of the pair loop in
+                                //           group order, with empty places (-1, 0) between
   int4* rows = nullptr;         // [nrows]   neighbour stencil of an i-group
   void* rec = nullptr;          // [n_max]   sorted particle records (T4)
   void* acc_pm = nullptr;       // [n_max]   PM acceleration in sorted order (T4)
@@ -146,7 +146,6 @@ struct p3m_plan {
   int tab64_var = 0;            // FP64 split table: the same, and the number of
   double tab64_v0 = 0, tab64_v1 = 0;  // leading pieces evaluated exactly
   int tab64_exact = 0;
-  int scan_tmp_len = 0;
   int count_dirty = 1;          // cell counts not known to be zero (set until a binning's scan)
   p3m::Workspace ws;
   // stage timers: events [call][2 * stage + {0: start, 1: end}]
@@ -161,16 +160,13 @@ namespace p3m {
 
 // Launchers (each enqueues on plan->stream; returns hipSuccess or the error).
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
-hipError_t launch_scan(int32_t* in, int32_t* out, int64_t len, int32_t* tmp, hipStream_t s,
-                       bool zero_in = false);
-int scan_tmp_size(int64_t len);
-int items_tmp_size(int64_t ngroup);   // block sums of the work-list scan
+int scan_tiles(int64_t ncell);        // tiles of the cell counts' scan
 
+// The pair loop's work list: none, in chunks of kChunk with one wave each
+// (whole), or cut as pair_split says.
+enum class Items { kNone, kWhole, kCut };
 hipError_t launch_bin(p3m_plan* P, int64_t n, const double* pos, const double* mass,
-                      double mass_scalar);
-// The work list of n binned particles, cut as pair_split says (whole: in
-// chunks of kChunk, one wave each).
-hipError_t launch_items(p3m_plan* P, int64_t n, bool whole);
+                      double mass_scalar, Items items);
 
 template <typename T>
 hipError_t launch_deposit(p3m_plan* P);

@@ -76,7 +76,7 @@ struct PairArgs {
   const int32_t* __restrict__ skey;
   const int32_t* __restrict__ start;
   const int2* __restrict__ items;
-  const int32_t* __restrict__ n_items;
+  int n_items;                          // places in the list (some empty)
   int chunk;                            // i-particles per item (kChunk in the one-sided sum)
   const int4* __restrict__ rows;
   int nrows;
@@ -1109,8 +1109,9 @@ k_pairs(PairArgs<T> A) {
   // the eight XCDs then work on neighbouring groups at the same time, which
   // measured faster than giving each XCD its own slab of the box.
   const int item = (int)blockIdx.x;
-  if (item >= *A.n_items) return;
+  if (item >= A.n_items) return;
   const int2 it = A.items[item];
+  if (it.x < 0) return;
   const int lg = A.lg, lgG = A.lgG, G = A.G, GG = G * G;
   const int lgd = lg - lgG, md = (1 << lgd) - 1;
   const int gx0 = (it.x >> (2 * lgd)) << lgG;
@@ -1154,11 +1155,10 @@ k_pairs(PairArgs<T> A) {
   pair_dispatch<T, COUNT, UM, TAB, VJP, false, W>(A, S, gx0, gy0, gz0, ibeg, ni, it.x);
 }
 
-// Grid of the pair kernel: the call's item bound (every group that can hold
-// a particle, and a further item per whole chunk) rounded up to a multiple of
-// kXcds.
+// Grid of the pair kernel: the places of the work list (one a group and one
+// a whole chunk) rounded up to a multiple of kXcds.
 unsigned pair_grid(const p3m_plan* P, int64_t n) {
-  const int64_t items = std::min(P->ngroup, n) + n / P->chunk;
+  const int64_t items = P->ngroup + n / P->chunk;
   return (unsigned)((items + kXcds - 1) / kXcds * kXcds);
 }
 
@@ -1170,7 +1170,7 @@ PairArgs<T> make_args(p3m_plan* P, int64_t n) {
   A.skey = W.skey;
   A.start = W.start;
   A.items = W.items;
-  A.n_items = W.goff + P->ngroup;
+  A.n_items = (int)(P->ngroup + n / P->chunk);
   A.chunk = P->chunk;
   A.rows = W.rows;
   A.nrows = P->nrows;
