@@ -335,9 +335,10 @@ int p3m_stage_times(p3m_plan* plan, double* ms_out, int32_t n_stages);
  * `params` for n particles, computed by the same kernels, with every pair
  * evaluated from both sides. The call allocates nothing: its workspace is
  * one fixed device array of 12 MiB per GPU, held from the library's first
- * such call on that GPU until the process ends; the stencil rows and
- * split-factor tables are computed on the host and copied into it on
- * hip_stream (from host memory the call owns) before the kernels run.
+ * such call on that GPU until the process ends; the stencil rows and the
+ * split-factor table are computed on the host (the last parameters' are
+ * kept) and written into it by a kernel on hip_stream that carries them in
+ * its arguments, before the other kernels run.
  *   params      as for p3m_plan_create (all of it validated the same way;
  *               fd_order, deconv_power, adjoint and ewald_gridsize unused)
  *   n           0 <= n <= P3M_NOALLOC_MAX_N

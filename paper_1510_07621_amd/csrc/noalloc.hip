@@ -1,12 +1,14 @@
 // Short-range force without a plan: pp_force_noalloc, for callers that
 // cannot allocate device memory. Its workspace (binning arrays, work list,
 // stencil rows, split tables, sorted records) is carved from one file-scope
-// device array of fixed size; the stencil and the split tables are computed
-// on the host per call and copied in on the caller's stream. The arithmetic
+// device array of fixed size; the stencil and the split table are computed
+// on the host (once while the parameters stay) and handed over in the
+// arguments of the call's first kernel. The arithmetic
 // is that of pp_force (the same kernels), with every pair evaluated from
 // both sides.
 #include <cmath>
 #include <cstdint>
+#include <cstring>
 #include <mutex>
 
 #include "p3m_internal.h"
@@ -22,9 +24,113 @@ constexpr int kMaxRows = 4096;
 // from hipGetSymbolAddress, one per device.
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
-std::mutex g_mutex;                       // the address table and the host row buffer
+constexpr int kTabWords = 2 * p3m::kSplitCoef64 * (p3m::kSplitBins + 1);   // the longer table
+
+// The stencil rows and the split table of a set of parameters, as the words
+// k_setup unpacks. The last set is kept, by its values: a program that calls
+// in a loop keeps its parameters, and the fit of the table takes 0.2 (FP32)
+// to 0.6 ms (FP64) of host time, the call's kernels 0.1 ms.
+struct HostTables {
+  bool valid = false;
+  int precision = 0, G = 0;
+  double cutoff_rs = 0, soft_rs = 0, radius = 0;
+  p3m::SplitMap map{};
+  int nrows = 0, ntab = 0;
+  uint32_t words[kMaxRows + kTabWords];     // rows, then the table
+};
+
+std::mutex g_mutex;                       // the address table and the tables below
 void* g_scratch[kMaxDevices] = {};
-int32_t g_rows[8 * kMaxRows];
+HostTables g_tables;
+int32_t g_rows[4 * kMaxRows];
+
+// Makes g_tables those of plan P (P->nrows <= kMaxRows checked before).
+void make_tables(const p3m_plan& P) {
+  HostTables& H = g_tables;
+  const p3m_params& q = P.prm;
+  const double soft = q.softening / P.r_s, radius = P.r_c / P.h;
+  if (H.valid && H.precision == q.precision && H.G == P.G && H.cutoff_rs == q.cutoff_rs &&
+      H.soft_rs == soft && H.radius == radius)
+    return;
+  H.valid = false;
+  H.precision = q.precision;
+  H.G = P.G;
+  H.cutoff_rs = q.cutoff_rs;
+  H.soft_rs = soft;
+  H.radius = radius;
+  H.nrows = P.nrows;
+  // a row's four values in a byte each: at most 32 cells of reach (r_c below
+  // half a box of at most 64 cells) on either side of the group
+  p3m::stencil_rows(P.G, radius, g_rows, P.nrows);
+  for (int r = 0; r < P.nrows; ++r) {
+    uint32_t w = 0;
+    for (int c = 0; c < 4; ++c) w |= (uint32_t)(uint8_t)(int8_t)g_rows[4 * r + c] << (8 * c);
+    H.words[r] = w;
+  }
+  if (q.precision == P3M_FP32) {
+    float tab[4 * (p3m::kSplitBins + 1)];
+    H.map = p3m::split_table(q.cutoff_rs, soft, p3m::kSplitBins, tab);
+    H.ntab = sizeof(tab) / 4;
+    std::memcpy(H.words + H.nrows, tab, sizeof(tab));
+  } else {
+    double tab[p3m::kSplitCoef64 * (p3m::kSplitBins + 1)];
+    H.map = p3m::split_table64(q.cutoff_rs, soft, tab);
+    H.ntab = sizeof(tab) / 4;
+    std::memcpy(H.words + H.nrows, tab, sizeof(tab));
+  }
+  H.valid = true;
+}
+
+// Words [at, at + count) of the rows and the table, carried in the kernel's
+// arguments (a captured call replays with them, and no copy is queued).
+constexpr int kSetupWords = 960;
+struct SetupArgs {
+  int4* rows;
+  uint32_t* tab;
+  int nrows, at, count;
+  int32_t* clear;             // cell counts to clear (the first launch), or null
+  int nclear;
+  uint32_t words[kSetupWords];
+};
+static_assert(sizeof(SetupArgs) <= 4096, "kernel arguments");
+
+__global__ void __launch_bounds__(256) k_setup(SetupArgs A) {
+  const int stride = gridDim.x * blockDim.x, first = blockIdx.x * blockDim.x + threadIdx.x;
+  for (int i = first; i < A.count; i += stride) {
+    const uint32_t w = A.words[i];
+    const int k = A.at + i;
+    if (k < A.nrows)
+      A.rows[k] = make_int4((int8_t)w, (int8_t)(w >> 8), (int8_t)(w >> 16), (int8_t)(w >> 24));
+    else
+      A.tab[k - A.nrows] = w;
+  }
+  if (A.clear)
+    for (int i = first; i < A.nclear; i += stride) A.clear[i] = 0;
+}
+
+// The tables of g_tables into the plan's workspace, and the cell counts
+// cleared (the array keeps the last call's contents).
+hipError_t launch_setup(p3m_plan* P) {
+  const HostTables& H = g_tables;
+  const int total = H.nrows + H.ntab;
+  for (int at = 0; at < total; at += kSetupWords) {
+    SetupArgs A;
+    A.rows = P->ws.rows;
+    A.tab = H.precision == P3M_FP32 ? (uint32_t*)P->ws.split_tab : (uint32_t*)P->ws.split_tab64;
+    A.nrows = H.nrows;
+    A.at = at;
+    A.count = total - at < kSetupWords ? total - at : kSetupWords;
+    A.clear = at == 0 ? P->ws.count : nullptr;
+    A.nclear = (int)P->ncell;
+    std::memcpy(A.words, H.words + at, 4 * (size_t)A.count);
+    const unsigned blocks = (unsigned)(at == 0 && P->ncell > 4096 ? P->ncell / 1024 : 4);
+    k_setup<<<blocks, 256, 0, P->stream>>>(A);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  P->count_dirty = 0;
+  return hipSuccess;
+}
 
 // Device address of this device's scratch array (looked up once per device,
 // with that device current).
@@ -94,7 +200,6 @@ extern "C" int pp_force_noalloc(const p3m_params* params, int64_t n, const doubl
     return P3M_EINVAL;
   if (P.nrows > kMaxRows || carve(&P, nullptr, n) > kScratchBytes) return P3M_ESIZE;
   P.stream = (hipStream_t)hip_stream;
-  P.count_dirty = 1;             // the array keeps the last call's counts: clear them
   P.timing_slot = -1;
 
   std::lock_guard<std::mutex> lock(g_mutex);
@@ -106,7 +211,9 @@ extern "C" int pp_force_noalloc(const p3m_params* params, int64_t n, const doubl
   if ((e = scratch_address(dev, &base)) != hipSuccess) return status_of(e);
   P.device = dev;
   carve(&P, base, n);
-  if ((e = p3m::plan_upload_tables(&P, g_rows)) != hipSuccess) return status_of(e);
+  make_tables(P);
+  p3m::plan_set_split(&P, g_tables.map);
+  if ((e = launch_setup(&P)) != hipSuccess) return status_of(e);
   if ((e = p3m::launch_bin(&P, n, pos, mass, mass_scalar, p3m::Items::kCut)) != hipSuccess)
     return status_of(e);
   e = params->precision == P3M_FP32

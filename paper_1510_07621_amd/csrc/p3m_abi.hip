@@ -608,10 +608,25 @@ int plan_geometry(const p3m_params& q, int64_t n_max, p3m_plan* P) {
   P->ngd = q.grid_n / P->G;
   P->ngroup = (int64_t)P->ngd * P->ngd * P->ngd;
   P->nrows = stencil_rows(P->G, r_c / h, nullptr, 0);
-  P->nseg = segment_rows(P->G, r_c / h, nullptr, 0, &P->npos);
+  if (P->nrows < 0) return P->nrows;
+  P->nseg = P->npos = 0;
+  if (q.pair_partials > 0) P->nseg = segment_rows(P->G, r_c / h, nullptr, 0, &P->npos);
   if (P->nseg < 0) return P->nseg;
   P->max_items = P->ngroup + n_max / kMinChunk;
   return P3M_OK;
+}
+
+void plan_set_split(p3m_plan* P, const SplitMap& m) {
+  if (P->prm.precision == P3M_FP32) {
+    P->tab_var = m.var;
+    P->tab_v0 = m.v0 * P->r_s;
+    P->tab_v1 = m.v1 * P->r_s;
+  } else {
+    P->tab64_var = m.var;
+    P->tab64_v0 = m.v0 * P->r_s;
+    P->tab64_v1 = m.v1 * P->r_s;
+    P->tab64_exact = m.exact;
+  }
 }
 
 hipError_t plan_upload_tables(p3m_plan* P, int32_t* rows_host) {
@@ -661,21 +676,15 @@ hipError_t plan_upload_tables(p3m_plan* P, int32_t* rows_host) {
       err = hipMemcpyAsync(P->ws.pboff, off, sizeof(int32_t) * (nb + 1), hipMemcpyHostToDevice,
                            P->stream);
   }
-  if (err == hipSuccess) {
+  // the split table of the plan's precision (the FP64 fit takes 0.6 ms)
+  if (err == hipSuccess && q.precision == P3M_FP32) {
     float tab[4 * (kSplitBins + 1)];
-    SplitMap m = split_table(q.cutoff_rs, q.softening / P->r_s, kSplitBins, tab);
-    P->tab_var = m.var;
-    P->tab_v0 = m.v0 * P->r_s;
-    P->tab_v1 = m.v1 * P->r_s;
+    plan_set_split(P, split_table(q.cutoff_rs, q.softening / P->r_s, kSplitBins, tab));
     err = hipMemcpyAsync(P->ws.split_tab, tab, sizeof(tab), hipMemcpyHostToDevice, P->stream);
   }
-  if (err == hipSuccess) {
+  if (err == hipSuccess && q.precision == P3M_FP64) {
     double tab64[kSplitCoef64 * (kSplitBins + 1)];
-    SplitMap m = split_table64(q.cutoff_rs, q.softening / P->r_s, tab64);
-    P->tab64_var = m.var;
-    P->tab64_v0 = m.v0 * P->r_s;
-    P->tab64_v1 = m.v1 * P->r_s;
-    P->tab64_exact = m.exact;
+    plan_set_split(P, split_table64(q.cutoff_rs, q.softening / P->r_s, tab64));
     err = hipMemcpyAsync(P->ws.split_tab64, tab64, sizeof(tab64), hipMemcpyHostToDevice,
                          P->stream);
   }

@@ -246,10 +246,10 @@ int segment_rows(int g, double radius_cells, int32_t* out, int cap, int* npos);
 // p3m_plan_create) and the plan's geometry: grid, split and cutoff lengths,
 // i-group edge, stencil row count, work-list bound. Allocates nothing.
 int plan_geometry(const p3m_params& q, int64_t n_max, p3m_plan* P);
-// The stencil rows (computed into rows_host, P->nrows entries of 4 int32)
-// and the split-factor tables copied into the plan's workspace on its
-// stream (pageable host sources: each copy has read its source on return);
-// sets the plan's table maps.
+// The stencil rows (computed into rows_host, P->nrows entries of 4 int32, and
+// the segments after them) and the split-factor table of the plan's precision
+// copied into the plan's workspace on its stream (pageable host sources: each
+// copy has read its source on return); sets the plan's table map.
 hipError_t plan_upload_tables(p3m_plan* P, int32_t* rows_host);
 // Split-factor table: out[c * (bins + 1) + k] is coefficient c of bin k of
 // the cubic pieces over v in [v0, v1] (units of r_s); var 0: v = r / r_s,
@@ -260,6 +260,8 @@ struct SplitMap {
   int exact;    // FP64: leading pieces the kernel replaces by the exact formula
 };
 SplitMap split_table(double cutoff_rs, double soft_rs, int bins, float* out);
+// The plan's map of its precision's split table.
+void plan_set_split(p3m_plan* P, const SplitMap& m);
 // FP64 table: out[l * (kSplitBins + 1) + k] is the coefficient of t^l
 // (t in [0, 1) across the bin) of piece k of the same variable choice; entry kSplitBins is
 // the constant value at v1.

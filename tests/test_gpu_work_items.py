@@ -67,3 +67,22 @@ def test_one_sided_above_its_line(precision, tol, kind, n, grid):
             out.append(host(P.pp_force(x, md) if kind == "force" else P.pp_force_vjp(x, md, lam)))
     for got in out[1:]:
         assert metrics.force_errors(got, out[0])["global"] <= (1 if kind == "force" else 10) * tol
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32", 1e-5)])
+def test_noalloc_follows_its_parameters(precision, tol):
+    """pp_force_noalloc keeps the tables of the last parameters: calls that
+    change the cutoff, the grid, the softening or the particle number and
+    come back equal the plan's force each time, also with a stencil of
+    thousands of rows (several launches to hand it over)."""
+    from paper_1510_07621_amd import binding
+    calls = [(5000, dict(grid_n=32)), (5000, dict(grid_n=32, cutoff_rs=6.0)),
+             (3001, dict(grid_n=64, rs_cells=4.0, cutoff_rs=6.0)), (5000, dict(grid_n=32)),
+             (5000, dict(grid_n=32, softening=0.3 / 32)), (301, dict(grid_n=32, softening=0.3 / 32))]
+    for n, kw in calls:
+        prm = binding.Params(precision=precision, **kw)
+        x = dev(ics.uniform(n, seed=n))
+        got = host(binding.pp_force_noalloc(prm, x, 1.0 / n))
+        with binding.Plan(prm, n) as P:
+            want = host(P.pp_force(x, 1.0 / n))
+        assert metrics.force_errors(got, want)["global"] <= tol
