@@ -6,8 +6,8 @@
 // each axis with weights 1 - t and t (nodes at c h, periodic), so a brick's
 // particles touch one node more per axis than it has cells.
 //
-// Deposit: each brick's 8^3 nodes gather the particles of the cells around
-// them (no atomics; see k_deposit_gather). The density is rho = sum m W / h^3.
+// Deposit: each brick's nodes add the corner sums of the cells around them (no
+// atomics; see k_deposit_cells). The density is rho = sum m W / h^3.
 //
 // Interpolation (bricks of BX x BX x BZ cells, 4 x 4 x 16): the brick's
 // potential plus a two-node halo, (BX + 5)^2 (BZ + 5) values, is staged in
@@ -24,129 +24,110 @@ namespace {
 
 using namespace brick;
 
-// Deposit by gathering: the workgroup owns the 8^3 nodes of its brick (every
-// grid node belongs to exactly one brick, so each is written once, with no
-// atomics and in a fixed order). Node n takes, per axis, weight t from the
-// particles of cell n - 1 (n is that cell's upper node) and 1 - t from those
-// of cell n, so the 8^3 nodes need the cells [-1, 8)^3 around the brick,
-// whose sorted ranges are staged in LDS first. NC = 1: mass, scaled by
-// 1 / h^3 (the density); NC = 3: mass times each component of a cotangent
-// (the adjoint's deposit), unscaled, to out[c * ng^3 + node].
+// Deposit by cells: the workgroup owns the BX x BY x BZ nodes of its brick
+// (every grid node belongs to exactly one brick, so each is written once, with
+// no atomics and in a fixed order). A node takes, per axis, the upper-corner
+// share of the cell below it and the lower-corner share of its own, so the
+// brick needs the cells [-1, B) around it on each axis. One thread a cell sums
+// the cell's particles into its eight corners, which go to LDS; then one
+// thread a node adds the one corner it takes from each of its eight cells.
+// Each particle is read once a brick that sees its cell (1.7 times on
+// average) and its weights are formed once. (A node that looped over the
+// particles of its eight cells read and weighted each particle eight times:
+// 256^3 lattice FP32 362 -> 185 us, clustered 862 -> 373; the cotangent's
+// deposit on 2M clustered particles 697 -> 213. What is left is the loop over
+// a cell's particles, as long as the wave's fullest cell.) NC = 1: mass, scaled by 1 / h^3
+// (the density); NC = 3: mass times each component of a cotangent (the
+// adjoint's deposit), unscaled, to out[c * ng^3 + node].
 //
-// Heavy cells (NC = 1): a node thread that loops over the particles of its
-// eight cells takes as long as the most crowded of them, so on clustered
-// input a few threads would hold their brick for thousands of iterations.
-// A cell with more than kHeavy particles is instead reduced once, by one
-// wave (the lanes split its particles), into its eight corner sums
-// sum m (1 - t or t)_x (1 - t or t)_y (1 - t or t)_z, kept in LDS for up to
-// kHeavySlots such cells per brick; its nodes add the one sum each needs.
-// (Further heavy cells of a brick are looped over as before.)
+// A cell with more than kHeavy particles is summed by a whole wave (the lanes
+// split its particles), so that a crowded cell does not hold up its brick.
 constexpr int kHeavy = 16;
-constexpr int kHeavySlots = 96;
 
 template <typename T, int NC>
+__device__ __forceinline__ void add_corners(T (&m)[8 * NC], typename Vec<T>::v4 p,
+                                            const typename Vec<T>::v4* __restrict__ lam, int s,
+                                            T inv_h) {
+  const T tx = p.x * inv_h, ty = p.y * inv_h, tz = p.z * inv_h;
+  const T wx[2] = {T(1) - tx, tx}, wy[2] = {T(1) - ty, ty}, wz[2] = {T(1) - tz, tz};
+  typename Vec<T>::v4 l;
+  if constexpr (NC == 3) l = lam[s];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const T w = wx[q >> 2] * wy[(q >> 1) & 1] * wz[q & 1];
+    if constexpr (NC == 1) {
+      m[q] += p.w * w;
+    } else {
+      const T mw = p.w * w;
+      m[3 * q] += mw * l.x;
+      m[3 * q + 1] += mw * l.y;
+      m[3 * q + 2] += mw * l.z;
+    }
+  }
+}
+
+template <typename T, int NC, int BX, int BY, int BZ>
 __global__ void __launch_bounds__(kThreads)
-k_deposit_gather(const typename Vec<T>::v4* __restrict__ rec,
-                 const typename Vec<T>::v4* __restrict__ lam, const int32_t* __restrict__ start,
-                 int ng, int lg, T inv_h, T scale, T* __restrict__ out) {
-  constexpr int kC = kN1 * kN1 * kN1;             // cells [-1, kBrick)^3
-  constexpr bool HV = NC == 1;                    // heavy cells reduced once
-  __shared__ int cs[kC], cn[kC];
-  __shared__ short hidx[HV ? kC : 1];             // slot of a heavy cell, or -1
-  __shared__ short hcell[HV ? kHeavySlots : 1];
-  __shared__ T mom[HV ? kHeavySlots : 1][8];
-  __shared__ int hcount;
-  const int lb = lg - 3, mb = (1 << lb) - 1, mask = ng - 1;
+k_deposit_cells(const typename Vec<T>::v4* __restrict__ rec,
+                const typename Vec<T>::v4* __restrict__ lam, const int32_t* __restrict__ start,
+                int ng, int lg, T inv_h, T scale, T* __restrict__ out) {
+  constexpr int CY = BY + 1, CZ = BZ + 1, kC = (BX + 1) * CY * CZ;
+  __shared__ T corner[8 * NC][kC];
+  __shared__ int heavy[kC];
+  __shared__ int nheavy;
+  const int mask = ng - 1, nbz = ng / BZ, nby = ng / BY;
   const int b = blockIdx.x;
-  const int bz0 = (b & mb) * kBrick, by0 = ((b >> lb) & mb) * kBrick, bx0 = (b >> (2 * lb)) * kBrick;
-  if (HV && threadIdx.x == 0) hcount = 0;
+  const int bz0 = (b % nbz) * BZ, by0 = ((b / nbz) % nby) * BY, bx0 = (b / (nbz * nby)) * BX;
+  const auto cell_of = [&](int e) {
+    const int gx = (bx0 - 1 + e / (CY * CZ)) & mask, gy = (by0 - 1 + (e / CZ) % CY) & mask,
+              gz = (bz0 - 1 + e % CZ) & mask;
+    return (((gx << lg) | gy) << lg) | gz;
+  };
+  if (threadIdx.x == 0) nheavy = 0;
+  __syncthreads();
   for (int e = threadIdx.x; e < kC; e += kThreads) {
-    const int gx = (bx0 - 1 + e / (kN1 * kN1)) & mask, gy = (by0 - 1 + (e / kN1) % kN1) & mask,
-              gz = (bz0 - 1 + e % kN1) & mask;
-    const int64_t c = (((int64_t)gx << lg | gy) << lg) | gz;
-    const int lo = start[c];
-    cs[e] = lo;
-    cn[e] = start[c + 1] - lo;
+    const int c = cell_of(e);
+    const int s0 = start[c], s1 = start[c + 1];
+    if (s1 - s0 > kHeavy) {
+      heavy[atomicAdd(&nheavy, 1)] = e;
+      continue;
+    }
+    T m[8 * NC];
+#pragma unroll
+    for (int q = 0; q < 8 * NC; ++q) m[q] = T(0);
+    for (int s = s0; s < s1; ++s) add_corners<T, NC>(m, rec[s], lam, s, inv_h);
+#pragma unroll
+    for (int q = 0; q < 8 * NC; ++q) corner[q][e] = m[q];
   }
   __syncthreads();
-  if constexpr (HV) {
-    for (int e = threadIdx.x; e < kC; e += kThreads) {
-      short slot = -1;
-      if (cn[e] > kHeavy) {
-        const int k = atomicAdd(&hcount, 1);
-        if (k < kHeavySlots) {
-          slot = (short)k;
-          hcell[k] = (short)e;
-        }
-      }
-      hidx[e] = slot;
+  const int nh = nheavy, lane = threadIdx.x & 63;
+  for (int k = threadIdx.x >> 6; k < nh; k += kThreads / 64) {
+    const int e = heavy[k], c = cell_of(e);
+    const int s0 = start[c], s1 = start[c + 1];
+    T m[8 * NC];
+#pragma unroll
+    for (int q = 0; q < 8 * NC; ++q) m[q] = T(0);
+    for (int s = s0 + lane; s < s1; s += 64) add_corners<T, NC>(m, rec[s], lam, s, inv_h);
+#pragma unroll
+    for (int q = 0; q < 8 * NC; ++q) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) m[q] += __shfl_xor(m[q], o, 64);
+      if (lane == 0) corner[q][e] = m[q];
     }
-    __syncthreads();
-    const int nh = min(hcount, kHeavySlots);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int k = wave; k < nh; k += kThreads / 64) {
-      const int e = hcell[k];
-      const int s0 = cs[e], s1 = s0 + cn[e];
-      T m8[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) m8[q] = T(0);
-      for (int s = s0 + lane; s < s1; s += 64) {
-        const typename Vec<T>::v4 p = rec[s];
-        const T tx = p.x * inv_h, ty = p.y * inv_h, tz = p.z * inv_h;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int a = q >> 2, bb = (q >> 1) & 1, c = q & 1;
-          m8[q] += p.w * ((a ? T(1) - tx : tx) * (bb ? T(1) - ty : ty) * (c ? T(1) - tz : tz));
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) m8[q] += __shfl_xor(m8[q], o, 64);
-      }
-      if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) mom[k][q] = m8[q];
-      }
-    }
-    __syncthreads();
   }
+  __syncthreads();
   const int64_t ncell = (int64_t)1 << (3 * lg);
-  for (int node = threadIdx.x; node < kBrick * kBrick * kBrick; node += kThreads) {
-    const int i = node >> 6, j = (node >> 3) & 7, k = node & 7;
+  for (int node = threadIdx.x; node < BX * BY * BZ; node += kThreads) {
+    const int k = node % BZ, j = (node / BZ) % BY, i = node / (BZ * BY);
     T acc[NC];
 #pragma unroll
     for (int q = 0; q < NC; ++q) acc[q] = T(0);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int d = 0; d < 8; ++d) {
+      const int e = ((i + (d >> 2)) * CY + (j + ((d >> 1) & 1))) * CZ + (k + (d & 1));
 #pragma unroll
-      for (int bb = 0; bb < 2; ++bb)
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-          const int e = ((i + a) * kN1 + (j + bb)) * kN1 + (k + c);
-          if constexpr (HV) {
-            const int h = hidx[e];
-            if (h >= 0) {
-              acc[0] += mom[h][(a << 2) | (bb << 1) | c];
-              continue;
-            }
-          }
-          const int s0 = cs[e], s1 = s0 + cn[e];
-          for (int s = s0; s < s1; ++s) {
-            const typename Vec<T>::v4 p = rec[s];
-            const T tx = p.x * inv_h, ty = p.y * inv_h, tz = p.z * inv_h;
-            const T w = (a ? T(1) - tx : tx) * (bb ? T(1) - ty : ty) * (c ? T(1) - tz : tz);
-            if constexpr (NC == 1) {
-              acc[0] += p.w * w;
-            } else {
-              const typename Vec<T>::v4 l = lam[s];
-              const T mw = p.w * w;
-              acc[0] += mw * l.x;
-              acc[1] += mw * l.y;
-              acc[2] += mw * l.z;
-            }
-          }
-        }
+      for (int q = 0; q < NC; ++q) acc[q] += corner[NC * (7 - d) + q][e];
+    }
     const int64_t g = (((int64_t)(bx0 + i) << lg | (by0 + j)) << lg) | (bz0 + k);
 #pragma unroll
     for (int q = 0; q < NC; ++q) out[q * ncell + g] = acc[q] * scale;
@@ -235,23 +216,27 @@ k_interp(const typename Vec<T>::v4* __restrict__ rec, const int32_t* __restrict_
 
 }  // namespace
 
+template <typename T, int NC, int BX, int BY, int BZ>
+void deposit_bricks(p3m_plan* P, const void* lam, T scale, void* out) {
+  const unsigned nb = (unsigned)(P->ncell / (BX * BY * BZ));
+  k_deposit_cells<T, NC, BX, BY, BZ><<<nb, kThreads, 0, P->stream>>>(
+      (const typename Vec<T>::v4*)P->ws.rec, (const typename Vec<T>::v4*)lam, P->ws.start, P->ng,
+      P->lg, T(1.0 / P->h), scale, (T*)out);
+}
+
 template <typename T>
 hipError_t launch_deposit(p3m_plan* P) {
-  Workspace& W = P->ws;
-  const int nb = (int)(P->ncell / (kBrick * kBrick * kBrick));
-  k_deposit_gather<T, 1><<<nb, kThreads, 0, P->stream>>>(
-      (const typename Vec<T>::v4*)W.rec, nullptr, W.start, P->ng, P->lg, T(1.0 / P->h),
-      T(1.0 / (P->h * P->h * P->h)), (T*)W.grid);
+  // Bricks of 4 x 4 x 16 nodes in FP32 (14 KB of corner sums), 4 x 4 x 8 in
+  // FP64: 128^3 lattice 24 us (8^3 27, 8 x 8 x 16 32, 4 x 4 x 8 28), FP64 32
+  // us (4 x 4 x 16 34, 8^3 38); 2M clustered 53 and 73 us (8^3 62 and 99).
+  constexpr int BZ = sizeof(T) == 4 ? 16 : 8;
+  deposit_bricks<T, 1, 4, 4, BZ>(P, nullptr, T(1.0 / (P->h * P->h * P->h)), P->ws.grid);
   return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_deposit3(p3m_plan* P, const void* lam, void* grids) {
-  Workspace& W = P->ws;
-  const int nb = (int)(P->ncell / (kBrick * kBrick * kBrick));
-  k_deposit_gather<T, 3><<<nb, kThreads, 0, P->stream>>>(
-      (const typename Vec<T>::v4*)W.rec, (const typename Vec<T>::v4*)lam, W.start, P->ng, P->lg,
-      T(1.0 / P->h), T(1), (T*)grids);
+  deposit_bricks<T, 3, 4, 4, 16>(P, lam, T(1), grids);
   return hipGetLastError();
 }
 

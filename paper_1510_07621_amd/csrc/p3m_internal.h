@@ -22,7 +22,6 @@ template <> struct Vec<double> {
 };
 
 constexpr int kPairCap = 128;     // j-particles staged in LDS per pass of the pair loop
-constexpr int kBrick = 8;         // cells per brick edge (deposit, interpolation)
 constexpr int kChunk = 64;        // i-particles per pair-loop work item (one wavefront)
 constexpr int kMinChunk = 16;     // the smallest chunk that small sets are cut into
 // Calls of up to this many particles evaluate every pair from both sides
