@@ -51,11 +51,14 @@ namespace p3m {
 namespace {
 
 constexpr int kDesc = 3 * 64;          // runs per batch of 64 rows
+constexpr int kNoReaction = -2147483647 - 1;
 // j-particles staged in LDS per pass: kPairCap for the FP32 force, half that
 // for FP64 and for the adjoint (which stages the cotangents too), so that the
-// workgroup's LDS leaves room for the waves per SIMD that kPairWaves asks the
-// compiler to fit in registers (FP32 force 5, FP64 force 4, FP32 adjoint 4,
-// FP64 adjoint 3; measured best).
+// workgroup's LDS leaves room for the waves per SIMD that its registers allow:
+// FP32 5.0 KB, adjoint 4.8 KB and FP64 7.4 KB, 5 waves; FP64 adjoint 9.5 KB, 4.
+// (FP32, 192 entries: 128^3 lattice 2.25 -> 2.21 ms, but sparse sets 240 ->
+// 246 us and the one-sided sum 30.8 -> 31.0 ms; 256: 34.0 ms at 4 waves. FP32
+// adjoint, 128 entries: 4.04 -> 4.30 ms.)
 template <typename T, bool VJP> struct Stage {
   static constexpr int kCap = sizeof(T) == 4 && !VJP ? kPairCap : kPairCap / 2;
   static constexpr int kPer = kCap / 64;   // consecutive staged entries per lane
@@ -63,7 +66,9 @@ template <typename T, bool VJP> struct Stage {
 // At most kStreams streams (without clamped reads), so kStreams far sentinels
 // after the staged entries cover every read past the end.
 constexpr int kStreams = 16;
-// Waves per SIMD the compiler must leave room for (caps the registers).
+// Waves per SIMD the compiler must leave room for (caps the registers; FP64
+// and the adjoints fit in one more without being asked, and asking cost them
+// up to 4 %).
 template <typename T, bool VJP>
 constexpr int kPairWaves = sizeof(T) == 4 ? (VJP ? 4 : 5) : (VJP ? 3 : 4);
 // A coordinate far outside any box: its squared separation from any real
@@ -351,14 +356,42 @@ __device__ __forceinline__ void pair_vjp_weights(double r2, const PairArgs<doubl
   w2 = inv3 * (d - A.vjp_k5 * f * inv2);
 }
 
-__device__ __forceinline__ int wave_inclusive(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
+// Scans and reductions over a wave by DPP: shifts by 1, 2, 4 and 8 within
+// rows of 16 lanes, then the last lane of a row broadcast to the next row
+// (rows 1 and 3) and lane 31 to rows 2 and 3. Six dependent operations in
+// registers; the LDS permutes of __shfl take that many round trips of the
+// LDS, which is what an item of few particles waits for.
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ int dpp_or(int old, int v) {   // old where no lane is read
+  return __builtin_amdgcn_update_dpp(old, v, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS = 0xF>
+__device__ __forceinline__ float dpp_or(float old, float v) {
+  return __int_as_float(dpp_or<CTRL, ROWS>(__float_as_int(old), __float_as_int(v)));
+}
+// Inclusive scan with op, `none` its neutral element; lane 63 holds the total.
+template <typename V, typename OP>
+__device__ __forceinline__ V wave_scan(V v, V none, OP op) {
+  v = op(v, dpp_or<0x111>(none, v));          // row_shr:1
+  v = op(v, dpp_or<0x112>(none, v));          // row_shr:2
+  v = op(v, dpp_or<0x114>(none, v));          // row_shr:4
+  v = op(v, dpp_or<0x118>(none, v));          // row_shr:8
+  v = op(v, dpp_or<0x142, 0xA>(none, v));     // row_bcast:15 into rows 1 and 3
+  v = op(v, dpp_or<0x143, 0xC>(none, v));     // row_bcast:31 into rows 2 and 3
   return v;
+}
+__device__ __forceinline__ int wave_inclusive(int v) {
+  return wave_scan(v, 0, [](int a, int b) { return a + b; });
+}
+__device__ __forceinline__ int last_lane(int v) { return __builtin_amdgcn_readlane(v, 63); }
+__device__ __forceinline__ float last_lane(float v) {
+  return __int_as_float(last_lane(__float_as_int(v)));
+}
+__device__ __forceinline__ float wave_min(float v) {
+  return last_lane(wave_scan(v, __builtin_inff(), [](float a, float b) { return fminf(a, b); }));
+}
+__device__ __forceinline__ float wave_max(float v) {
+  return last_lane(wave_scan(v, -__builtin_inff(), [](float a, float b) { return fmaxf(a, b); }));
 }
 
 // The bounding box of an item's i-particles (relative to the group's first
@@ -383,16 +416,39 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// One wave's staging area.
+// Offsets of a run in one word: x and y in 10 bits, z in 12, all signed (a
+// plan's cutoff is below half of at most 512 cells).
+__device__ __forceinline__ int run_word(int rx, int ry, int zs) {
+  return (rx & 0x3ff) | ((ry & 0x3ff) << 10) | (zs << 20);
+}
+
+// Every read of the j stage is clamped to its first sentinel: the sums whose
+// items take at most four i-slots a lane (all but the FP32 force), from both
+// sides.
+template <typename T, bool VJP, bool HALF>
+constexpr bool Clamped = !HALF && (sizeof(T) == 8 || VJP);
+
+// One wave's staging area. Its size sets the waves in flight (LDS is handed
+// out in 1280-byte pieces). With a run's offsets in one word beside its slot
+// instead of five arrays, the owners in the entries' place and one sentinel
+// where reads are clamped, the two-sided FP64 sum went from 9.5 to 7.4 KB (4
+// to 5 waves per SIMD) and its adjoint from 12.0 to 9.5 KB (3 to 4). With the
+// scans by DPP: 128^3 lattice FP32 2.35 -> 2.25 ms, FP64 6.02 -> 5.54 ms; 64^3
+// FP64 adjoint 1.55 -> 1.28 ms; one-sided 256^3 31.9 -> 31.0 ms.
 template <typename T, bool VJP, bool HALF>
 struct WaveShared {
-  typename Vec<T>::v4 jb[Stage<T, VJP>::kCap + kStreams];   // staged j (+ far sentinels)
-  typename Vec<T>::v4 jl[VJP ? Stage<T, VJP>::kCap + kStreams : 1];   // adjoint mode: staged j cotangents
-  int d_lo[kDesc], d_pre[kDesc + 1], d_zs[kDesc];
-  int d_rp[HALF ? kDesc : 1];              // one-sided sum: partial offset of each run's
-                                           // first entry in the item's reactions, or -1
-  int owner[Stage<T, VJP>::kCap];               // run of each staged entry of a chunk
-  int d_rx[64], d_ry[64];                  // x, y cell offsets of each row
+  static constexpr int kCap = Stage<T, VJP>::kCap;
+  // staged j (+ far sentinels: one where every read is clamped, else one a
+  // stream); before a chunk's entries are written, the run that owns each
+  // (owner[]) has its place here
+  typename Vec<T>::v4 jb[kCap + (Clamped<T, VJP, HALF> ? 1 : kStreams)];
+  typename Vec<T>::v4 jl[VJP ? kCap + (Clamped<T, VJP, HALF> ? 1 : kStreams) : 1];   // adjoint
+                                           // mode: staged j cotangents
+  // each run of a batch: slot of its entries less their place in the batch;
+  // x and y cell offset of its column and z-cell shift (run_word)
+  int2 d_run[kDesc];
+  int d_rp[HALF ? kDesc : 1];              // one-sided sum: the same for the item's
+                                           // reactions, or kNoReaction
   ItemBox<T> box;                          // the item's i-particles' bounding box
 };
 
@@ -605,8 +661,8 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
   constexpr bool SC = TAB == 1 && !COUNT;
   const T h = A.h;
   const T ps = sizeof(T) == 4 ? T(A.tab_s) : T(A.tab_s64);
-  auto coord = [&](int cell, T off) {
-    const T v = fma(T(cell), h, off);
+  auto coord = [&](T cell, T off) {
+    const T v = fma(cell, h, off);
     return SC ? v * ps : v;
   };
   // slot sets; the one-sided sum sums each staged entry's reaction over the
@@ -632,9 +688,9 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
     si[u] = i_lo[run] + (fi - i_pre[run]);
     const T4 pi = A.rec[si[u]];
     const int czi = A.skey[si[u]] & mask;
-    xi[u] = has ? coord(run >> lgG, pi.x) : T(kFar);
-    yi[u] = has ? coord(run & (G - 1), pi.y) : T(kFar);
-    zi[u] = has ? coord(czi - gz0, pi.z) : T(kFar);
+    xi[u] = has ? coord(T(run >> lgG), pi.x) : T(kFar);
+    yi[u] = has ? coord(T(run & (G - 1)), pi.y) : T(kFar);
+    zi[u] = has ? coord(T(czi - gz0), pi.z) : T(kFar);
     ax[u] = ay[u] = az[u] = T(0);
     if constexpr (HALF && !UM) mi[u] = pi.w;
     if constexpr (VJP) {
@@ -658,12 +714,8 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
         lo2 = fmin(lo2, zi[u]); hi2 = fmax(hi2, zi[u]);
       }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      lo0 = fmin(lo0, __shfl_xor(lo0, o, 64)); hi0 = fmax(hi0, __shfl_xor(hi0, o, 64));
-      lo1 = fmin(lo1, __shfl_xor(lo1, o, 64)); hi1 = fmax(hi1, __shfl_xor(hi1, o, 64));
-      lo2 = fmin(lo2, __shfl_xor(lo2, o, 64)); hi2 = fmax(hi2, __shfl_xor(hi2, o, 64));
-    }
+    lo0 = wave_min(lo0); lo1 = wave_min(lo1); lo2 = wave_min(lo2);
+    hi0 = wave_max(hi0); hi1 = wave_max(hi1); hi2 = wave_max(hi2);
     if (lane == 0) {
       S.box.lo[0] = lo0; S.box.lo[1] = lo1; S.box.lo[2] = lo2;
       S.box.hi[0] = hi0; S.box.hi[1] = hi1; S.box.hi[2] = hi2;
@@ -702,9 +754,9 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
       const int rc = cur.rf ? cur.cnt[0] : 0;
       const int rinc = wave_inclusive(rc);
       const int intra = i_pre[GG] - ibeg - ni;
-      S.d_rp[3 * lane] = cur.rf ? intra + rstaged + rinc - rc : -1;
-      S.d_rp[3 * lane + 1] = S.d_rp[3 * lane + 2] = -1;
-      rtotal = __builtin_amdgcn_readfirstlane(__shfl(rinc, 63, 64));
+      S.d_rp[3 * lane] = cur.rf ? intra + rstaged + rinc - rc - (inc - tot_l) : kNoReaction;
+      S.d_rp[3 * lane + 1] = S.d_rp[3 * lane + 2] = kNoReaction;
+      rtotal = last_lane(rinc);
     }
     int pre[3];
     {
@@ -712,16 +764,11 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         pre[k] = base;
-        S.d_lo[3 * lane + k] = cur.lo[k];
-        S.d_pre[3 * lane + k] = base;
-        S.d_zs[3 * lane + k] = cur.zs[k];
+        S.d_run[3 * lane + k] = make_int2(cur.lo[k] - base, run_word(cur.rx, cur.ry, cur.zs[k]));
         base += cur.cnt[k];
       }
     }
-    S.d_rx[lane] = cur.rx;
-    S.d_ry[lane] = cur.ry;
-    const int total = __builtin_amdgcn_readfirstlane(__shfl(inc, 63, 64));
-    if (lane == 63) S.d_pre[kDesc] = total;
+    const int total = last_lane(inc);
 
     for (int c0 = 0; c0 < total; c0 += kCap) {
       const int cn = min(kCap, total - c0);
@@ -729,13 +776,14 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
       // owner[q] = run of chunk entry q: each run marks its first entry in the
       // chunk, then a prefix maximum over the chunk fills the rest
       const int q0 = kStage * lane;
+      int* const owner = reinterpret_cast<int*>(S.jb);
 #pragma unroll
-      for (int e = 0; e < kStage; ++e) S.owner[q0 + e] = -1;
+      for (int e = 0; e < kStage; ++e) owner[q0 + e] = -1;
       wave_sync();
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         const int s = pre[k] - c0;
-        if (cur.cnt[k] > 0 && s + cur.cnt[k] > 0 && s < cn) S.owner[max(s, 0)] = 3 * lane + k;
+        if (cur.cnt[k] > 0 && s + cur.cnt[k] > 0 && s < cn) owner[max(s, 0)] = 3 * lane + k;
       }
       wave_sync();
       int dd[kStage];
@@ -743,18 +791,13 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
         int run = -1;
 #pragma unroll
         for (int e = 0; e < kStage; ++e) {
-          run = max(run, S.owner[q0 + e]);
+          run = max(run, owner[q0 + e]);
           dd[e] = run;
         }
+        wave_sync();       // the owners are read: their place may take entries
         // exclusive prefix maximum of the lanes' last values
-        int carry = run;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-          int t = __shfl_up(carry, o, 64);
-          if (lane >= o) carry = max(carry, t);
-        }
-        int before = __shfl_up(carry, 1, 64);
-        if (lane == 0) before = -1;
+        const int carry = wave_scan(run, -1, [](int a, int b) { return max(a, b); });
+        const int before = dpp_or<0x138>(-1, carry);      // wave_shr:1
 #pragma unroll
         for (int e = 0; e < kStage; ++e) dd[e] = max(dd[e], before);
       }
@@ -762,10 +805,12 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
       // loads in flight together
       {
         int src[kStage];
+        int2 run[kStage];
 #pragma unroll
         for (int e = 0; e < kStage; ++e) {
-          const int f = c0 + q0 + e;
-          src[e] = q0 + e < cn ? S.d_lo[dd[e]] + (f - S.d_pre[dd[e]]) : -1;
+          const bool in = q0 + e < cn;
+          run[e] = S.d_run[in ? dd[e] : 0];
+          src[e] = in ? run[e].x + (c0 + q0 + e) : -1;
         }
         T4 pj[kStage], lj[VJP ? kStage : 1];
         int cz[kStage];
@@ -780,11 +825,10 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
 #pragma unroll
         for (int e = 0; e < kStage; ++e) {
           if (src[e] >= 0) {
-            const int d = dd[e];
             T4 o;
-            o.x = coord(S.d_rx[d / 3], pj[e].x);
-            o.y = coord(S.d_ry[d / 3], pj[e].y);
-            o.z = coord(cz[e] + S.d_zs[d], pj[e].z);
+            o.x = coord(T((run[e].y << 22) >> 22), pj[e].x);
+            o.y = coord(T((run[e].y << 12) >> 22), pj[e].y);
+            o.z = coord(T(cz[e] + (run[e].y >> 20)), pj[e].z);
             o.w = pj[e].w;
             S.jb[q0 + e] = o;
             if constexpr (VJP) S.jl[q0 + e] = lj[e];
@@ -795,7 +839,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
         T4 far;
         far.x = far.y = far.z = T(-kFar);
         far.w = T(0);
-        if (lane < kStreams) S.jb[cn + lane] = far;
+        if (lane < (Clamped<T, VJP, HALF> ? 1 : kStreams)) S.jb[cn + lane] = far;
       }
       wave_sync();
       // lane (set, stream) takes staged entries st, st + ns, ...; the trip
@@ -945,7 +989,7 @@ __device__ __forceinline__ void pair_item(const PairArgs<T>& A, SH& B0, int gx0,
             if (P >= ni) idx = ibase + (P - ni);
           } else {
             const int rp = S.d_rp[dd[e]];
-            if (rp >= 0) idx = ibase + rp + (c0 + q - S.d_pre[dd[e]]);
+            if (rp != kNoReaction) idx = ibase + rp + (c0 + q);
           }
           if (idx >= 0 && idx < ptotal) {    // (always below: a guard only)
             const T4 r = S.jb[q];            // partial idx: 3 components together
@@ -1356,7 +1400,7 @@ template hipError_t launch_pairs<double>(p3m_plan*, int64_t, bool, void*, int, b
 template hipError_t launch_pair_count<double>(p3m_plan*, int64_t, int64_t*);
 #elif P3M_PAIR_PART == 2
 template hipError_t launch_pairs_vjp<float>(p3m_plan*, int64_t, bool, double*, bool, void*);
-#else
+#elif P3M_PAIR_PART == 3
 template hipError_t launch_pairs_vjp<double>(p3m_plan*, int64_t, bool, double*, bool, void*);
 #endif
 
