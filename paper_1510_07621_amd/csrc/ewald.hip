@@ -17,6 +17,8 @@
 // The pair sum: F_i = -G m_i sum_{j != i} m_j [ r / (|r|^2 + eps^2)^(3/2) + c(r) ],
 // r the minimum-image separation, all pairs, in FP64. A pair at zero
 // separation contributes nothing.
+#include <algorithm>
+
 #include "p3m_internal.h"
 
 namespace p3m {
@@ -130,6 +132,13 @@ __device__ __forceinline__ double3 ewald_corr(const double2* __restrict__ zp, in
   return c;
 }
 
+// 1 / sqrt(q), q > 0: the hardware estimate and one third-order step.
+__device__ __forceinline__ double rsqrt_pos(double q) {
+  const double y = __builtin_amdgcn_rsq(q);
+  const double e = fma(-q * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
+
 __device__ __forceinline__ double min_image(double d, double box, double inv_box) {
   return d - box * rint(d * inv_box);
 }
@@ -215,6 +224,142 @@ k_pp_ewald(int64_t n, const double* __restrict__ pos, const double* __restrict__
   }
 }
 
+// All pairs once: both terms of a pair are odd in the separation, so the force
+// on j is minus the one on i. The particles of the cell order are cut into
+// blocks of 64 and superblocks of kRotWaves blocks; a workgroup takes a pair
+// (I, J >= I) of superblocks, wave w the block w of I, one i a lane. For each
+// block of J a lane also holds one j, and the j's go round the wave lane by
+// lane (DPP wave_rol, their sums with them): in step s lane l evaluates i_l
+// with j_(l + s). Each particle's sum over a superblock has one writer, row J
+// of `part` for the i's and row I for the j's (the waves' shares of a j added
+// in wave order in LDS first), and k_ewald_combine adds the rows in order. A
+// superblock with itself is evaluated from both sides, without the j's share.
+// blockIdx.y: a share of the 64 steps, with rows of its own, for sets with too
+// few superblock pairs.
+//
+// What bounds the sum is the vector cache's rate of handing out a trilinear
+// cell's corners, 192 bytes a lane and pair: 60 accesses of the cache for a
+// 16-byte load of 64 lanes (TCP_TOTAL_CACHE_ACCESSES), 12 loads a step, and
+// 560 cycles a step and CU, of which arithmetic needs 180. Each pair once
+// halves the corners fetched. k_pp_ewald, then this kernel, 64^3 table: 32768
+// uniform particles 13.76 -> 7.80 ms, 20001 8.91 -> 4.10, 5000 1.12 -> 0.38;
+// 32768 clustered, 32^3 table 8.91 -> 5.12. (The table's columns of a tile
+// copied to LDS instead: 11.7 ms from both sides, bank conflicts taking 60 %
+// of the LDS time.)
+constexpr int kRotWaves = 8;
+constexpr int kRotSuper = 64 * kRotWaves;     // particles of a superblock
+
+__device__ __forceinline__ int wave_next(int v) {      // the next lane's value, round the wave
+  return __builtin_amdgcn_update_dpp(0, v, 0x134, 0xF, 0xF, false);
+}
+__device__ __forceinline__ double wave_next(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = wave_next((int)b), hi = wave_next((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+__global__ void __launch_bounds__(kRotSuper, 4)
+k_pp_ewald_blocks(int64_t n, const double* __restrict__ pos, const double* __restrict__ mass,
+                  double ms, double box, double eps2, const double2* __restrict__ tab, int E,
+                  int nsuper, const int32_t* __restrict__ order, double* __restrict__ part) {
+  __shared__ double red[3][kRotWaves][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the superblock pair: the blockIdx.x-th of (0, 0), (0, 1), .., (1, 1), ..
+  int I = 0, J = blockIdx.x;
+  while (J >= nsuper - I) {
+    J -= nsuper - I;
+    ++I;
+  }
+  J += I;
+  const int steps = 64 / gridDim.y, s0 = steps * blockIdx.y;
+  const double inv_box = 1.0 / box, inv_h = E / box;
+  const auto load = [&](int64_t slot, double& x, double& y, double& z, double& m) {
+    x = y = z = m = 0.0;                 // past the end: no mass
+    if (slot < n) {
+      const int64_t p = order[slot];
+      x = pos[p];
+      y = pos[n + p];
+      z = pos[2 * n + p];
+      m = mass ? mass[p] : ms;
+    }
+  };
+  const int64_t islot = (int64_t)I * kRotSuper + threadIdx.x;
+  double xi, yi, zi, mi;
+  load(islot, xi, yi, zi, mi);
+  double ax = 0, ay = 0, az = 0;
+  for (int b = 0; b < kRotWaves; ++b) {
+    const int64_t j0 = (int64_t)J * kRotSuper + 64 * b;
+    if (j0 >= n) break;                  // (uniform)
+    int jl = (lane + s0) & 63;           // the j this lane starts with
+    double xj, yj, zj, mj, bx = 0, by = 0, bz = 0;
+    load(j0 + jl, xj, yj, zj, mj);
+    for (int s = 0; s < steps; ++s) {
+      const double dx = min_image(xi - xj, box, inv_box);
+      const double dy = min_image(yi - yj, box, inv_box);
+      const double dz = min_image(zi - zj, box, inv_box);
+      const double r2 = dx * dx + dy * dy + dz * dz;
+      // (a pair at zero separation: finite weight times zero, and c(0) = 0)
+      const double inv = rsqrt_pos(r2 > 0.0 ? r2 + eps2 : 1.0);
+      const double w = inv * inv * inv;
+      const double3 c = ewald_corr(tab, E, inv_h, dx, dy, dz);
+      const double tx = dx * w + c.x, ty = dy * w + c.y, tz = dz * w + c.z;
+      ax += mj * tx;
+      ay += mj * ty;
+      az += mj * tz;
+      bx -= mi * tx;
+      by -= mi * ty;
+      bz -= mi * tz;
+      xj = wave_next(xj);
+      yj = wave_next(yj);
+      zj = wave_next(zj);
+      mj = wave_next(mj);
+      bx = wave_next(bx);
+      by = wave_next(by);
+      bz = wave_next(bz);
+      jl = wave_next(jl);
+    }
+    if (I == J) continue;                // (uniform)
+    __syncthreads();                     // the last block's shares are read
+    red[0][wave][jl] = bx;
+    red[1][wave][jl] = by;
+    red[2][wave][jl] = bz;
+    __syncthreads();
+    if (threadIdx.x < 3 * 64 && j0 + lane < n) {
+      double sum = 0;
+#pragma unroll
+      for (int v = 0; v < kRotWaves; ++v) sum += red[wave][v][lane];
+      part[3 * (((int64_t)blockIdx.y * nsuper + I) * n + j0 + lane) + wave] = sum;
+    }
+  }
+  if (islot < n) {
+    double* out = part + 3 * (((int64_t)blockIdx.y * nsuper + J) * n + islot);
+    out[0] = ax;
+    out[1] = ay;
+    out[2] = az;
+  }
+}
+
+// F of each particle, in input order, from the rows of sums.
+__global__ void __launch_bounds__(256)
+k_ewald_combine(int64_t n, const double* __restrict__ part, int rows,
+                const int32_t* __restrict__ order, const double* __restrict__ mass, double ms,
+                double negG, void* __restrict__ force, int force_fp32) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= 3 * n) return;
+  const int64_t slot = k / 3;
+  const int d = (int)(k - 3 * slot);
+  const int64_t i = order[slot];
+  double a = 0;
+#pragma unroll 8
+  for (int r = 0; r < rows; ++r) a += part[(int64_t)r * 3 * n + k];
+  const double f = negG * (mass ? mass[i] : ms) * a;
+  if (force_fp32)
+    ((float*)force)[d * n + i] = (float)f;
+  else
+    ((double*)force)[d * n + i] = f;
+}
+
 // The interpolated correction at given minimum-image separations.
 __global__ void __launch_bounds__(256)
 k_ewald_eval(int64_t npts, const double* __restrict__ r, double box,
@@ -232,6 +377,13 @@ k_ewald_eval(int64_t npts, const double* __restrict__ r, double box,
 
 }  // namespace
 
+static int ewald_supers(int64_t n) { return (int)((n + kRotSuper - 1) / kRotSuper); }
+
+int64_t ewald_part_size(int64_t n_max) {
+  const int64_t n = std::min(n_max, kEwaldBlocksMax);
+  return 3 * n * std::max<int64_t>(kEwaldRows, ewald_supers(n));
+}
+
 hipError_t launch_ewald_table(p3m_plan* P) {
   const int E = P->prm.ewald_gridsize, H = E / 2 + 1;
   const int total = H * H * H;
@@ -247,6 +399,20 @@ hipError_t launch_ewald_table(p3m_plan* P) {
 
 hipError_t launch_pp_ewald(p3m_plan* P, int64_t n, const double* pos, const double* mass,
                            double ms, const int32_t* order, void* force, int force_fp32) {
+  if (n <= kEwaldBlocksMax) {
+    const int nsuper = ewald_supers(n);
+    const int pairs = nsuper * (nsuper + 1) / 2;
+    int shares = 1;
+    while (shares < 8 && pairs * shares < 1024 && 2 * shares * nsuper <= kEwaldRows) shares *= 2;
+    k_pp_ewald_blocks<<<dim3((unsigned)pairs, (unsigned)shares), kRotSuper, 0, P->stream>>>(
+        n, pos, mass, ms, P->prm.box, P->eps * P->eps, (const double2*)P->ws.ewald_zpair,
+        P->prm.ewald_gridsize, nsuper, order, P->ws.ewald_part);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    k_ewald_combine<<<(unsigned)((3 * n + 255) / 256), 256, 0, P->stream>>>(
+        n, P->ws.ewald_part, nsuper * shares, order, mass, ms, -P->prm.G, force, force_fp32);
+    return hipGetLastError();
+  }
   const unsigned blocks = (unsigned)((n + kEwI - 1) / kEwI);
   k_pp_ewald<<<blocks, kEwThreads, 0, P->stream>>>(
       n, pos, mass, ms, P->prm.box, P->eps * P->eps, -P->prm.G,

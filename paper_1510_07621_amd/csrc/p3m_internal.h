@@ -88,6 +88,7 @@ struct Workspace {
   double* split_tab64 = nullptr;  // [kSplitCoef64][kSplitBins + 1] FP64 pieces of f(r)
   double* power_acc = nullptr;  // [3 * kMaxPowerBins + 2] power-spectrum sums
   void* ewald_tab = nullptr;    // [(E/2+1)^3] double4 Ewald correction octant (E > 0)
+  double* ewald_part = nullptr; // [rows][n][3] sums of the tabulated pair sum (ewald_part_size)
   void* ewald_zpair = nullptr;  // [(E/2+1)^2 (E/2)][3] double2: z-adjacent node pairs of it
   // one-sided pair sum between dense groups (Newton's third law; plans
   // with rcap > 0)
@@ -200,6 +201,12 @@ template <typename T>
 hipError_t launch_tables(p3m_plan* P);
 
 hipError_t launch_ewald_table(p3m_plan* P);
+// Particles up to which the tabulated pair sum evaluates each pair once (its
+// rows of sums, one a 512 particles, take 24 n^2 / 512 bytes: 200 MB there),
+// the rows a smaller set may use, and the doubles a plan holds for them.
+constexpr int64_t kEwaldBlocksMax = 65536;
+constexpr int kEwaldRows = 64;
+int64_t ewald_part_size(int64_t n_max);
 hipError_t launch_pp_ewald(p3m_plan* P, int64_t n, const double* pos, const double* mass,
                            double ms, const int32_t* order, void* force, int force_fp32);
 hipError_t launch_ewald_eval(p3m_plan* P, int64_t npts, const double* r, double* out);
