@@ -77,29 +77,27 @@ k_interp_vjp(const typename Vec<T>::v4* __restrict__ rec,
              int64_t n, double* __restrict__ pos_bar,
              const typename Vec<T>::v4* __restrict__ acc_pp) {
   constexpr int X1 = BX + 1, Z1 = BZ + 1;        // nodes touched per axis
-  constexpr int X5 = BX + 5, Z5 = BZ + 5;        // with the two-node gradient halo
-  __shared__ T ph[X5 * X5 * Z5];
+  using PR = PhiRows<BX, BZ>;
+  __shared__ __align__(16) T ph[PR::kSize];
   __shared__ T gr[3][X1 * X1 * Z1];
   __shared__ T ps[X1 * X1 * Z1];
   __shared__ InterpRuns<BX, BZ> R;
   const int mask = ng - 1, nbz = ng / BZ, nbx = ng / BX;
   const int b = blockIdx.x;
   const int bz0 = (b % nbz) * BZ, by0 = ((b / nbz) % nbx) * BX, bx0 = (b / (nbz * nbx)) * BX;
-  for (int i = threadIdx.x; i < X5 * X5 * Z5; i += kThreads) {
-    int nx = i / (X5 * Z5), ny = (i / Z5) % X5, nz = i % Z5;
-    int gx = (bx0 - 2 + nx) & mask, gy = (by0 - 2 + ny) & mask, gz = (bz0 - 2 + nz) & mask;
-    ph[i] = phi[(((int64_t)gx << lg | gy) << lg) | gz];
-  }
+  load_phi<T, BX, BZ>(ph, phi, lg, bx0, by0, bz0);
   for (int i = threadIdx.x; i < X1 * X1 * Z1; i += kThreads) {
-    int nx = i / (X1 * Z1), ny = (i / Z1) % X1, nz = i % Z1;
-    int gx = (bx0 + nx) & mask, gy = (by0 + ny) & mask, gz = (bz0 + nz) & mask;
+    const int row = small_div<Z1>(i), nz = i - row * Z1;
+    const int nx = small_div<X1>(row), ny = row - nx * X1;
+    const int gx = (bx0 + nx) & mask, gy = (by0 + ny) & mask, gz = (bz0 + nz) & mask;
     ps[i] = inv_h3 * psi[(((int64_t)gx << lg | gy) << lg) | gz];
   }
   load_interp_runs(R, start, lg, bx0, by0, bz0);  // contains __syncthreads
   for (int i = threadIdx.x; i < X1 * X1 * Z1; i += kThreads) {
-    int nx = i / (X1 * Z1), ny = (i / Z1) % X1, nz = i % Z1;
-    int q = ((nx + 2) * X5 + (ny + 2)) * Z5 + (nz + 2);
-    const int sx = X5 * Z5, sy = Z5, sz = 1;
+    const int row = small_div<Z1>(i), nz = i - row * Z1;
+    const int nx = small_div<X1>(row), ny = row - nx * X1;
+    const int q = PR::at(nx, ny, nz);
+    constexpr int sx = PR::kX * PR::kZ, sy = PR::kZ, sz = 1;
     gr[0][i] = c1 * (ph[q + sx] - ph[q - sx]) + c2 * (ph[q + 2 * sx] - ph[q - 2 * sx]);
     gr[1][i] = c1 * (ph[q + sy] - ph[q - sy]) + c2 * (ph[q + 2 * sy] - ph[q - 2 * sy]);
     gr[2][i] = c1 * (ph[q + sz] - ph[q - sz]) + c2 * (ph[q + 2 * sz] - ph[q - 2 * sz]);

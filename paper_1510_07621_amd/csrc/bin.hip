@@ -48,7 +48,8 @@ __device__ __forceinline__ int cell_coord(double t, int ng) {
 // as a caller that keeps its particles in the order of the last binning
 // hands it) share one atomic: the run's first lane adds the run's length
 // and each lane's rank is the old count plus its place in the run. With
-// input in random order every lane is a run of one.
+// input in random order every lane is a run of one. The cells are kept
+// (key) for the adjoint's sort of the cotangents only.
 __global__ void __launch_bounds__(256)
 k_bin_count(int64_t n, const double* __restrict__ pos, int ng, int lg, double inv_h,
             int32_t* __restrict__ key, int32_t* __restrict__ rank,
@@ -61,7 +62,7 @@ k_bin_count(int64_t n, const double* __restrict__ pos, int ng, int lg, double in
     int cy = cell_coord(pos[n + i] * inv_h, ng);
     int cz = cell_coord(pos[2 * n + i] * inv_h, ng);
     c = (((cx << lg) | cy) << lg) | cz;
-    key[i] = c;
+    if (key) key[i] = c;
   }
   const int lane = threadIdx.x & 63;
   const int prev = __shfl_up(c, 1, 64);
@@ -184,8 +185,7 @@ struct FinishArgs {
   const double* __restrict__ mass;
   double mass_scalar;
   int ng, lg;
-  double h;
-  const int32_t* __restrict__ key;
+  double h, inv_h;
   const int32_t* __restrict__ rank;
   const int32_t* __restrict__ lstart;
   const int32_t* __restrict__ tile;
@@ -254,14 +254,16 @@ k_bin_finish(FinishArgs<T> A) {
   if (b < A.scatter_blocks) {
     const int64_t n = A.n, i = (int64_t)b * kThreads + threadIdx.x;
     if (i >= n) return;
-    const int c = A.key[i];
+    // the cell again, as k_bin_count formed it: the positions are read anyway
+    const double x = A.pos[i], y = A.pos[n + i], z = A.pos[2 * n + i];
+    const int cx = cell_coord(x * A.inv_h, A.ng), cy = cell_coord(y * A.inv_h, A.ng),
+              cz = cell_coord(z * A.inv_h, A.ng);
+    const int c = (((cx << A.lg) | cy) << A.lg) | cz;
     const int dst = first(c) + A.rank[i];
-    const int mask = A.ng - 1;
-    const int cz = c & mask, cy = (c >> A.lg) & mask, cx = c >> (2 * A.lg);
     typename Vec<T>::v4 r;
-    r.x = (T)(A.pos[i] - cx * A.h);
-    r.y = (T)(A.pos[n + i] - cy * A.h);
-    r.z = (T)(A.pos[2 * n + i] - cz * A.h);
+    r.x = (T)(x - cx * A.h);
+    r.y = (T)(y - cy * A.h);
+    r.z = (T)(z - cz * A.h);
     r.w = (T)(A.mass ? A.mass[i] : A.mass_scalar);
     A.rec[dst] = r;
     A.perm[dst] = (int32_t)i;
@@ -382,7 +384,7 @@ static hipError_t launch_finish(p3m_plan* P, int64_t n, const double* pos, const
   A.ng = P->ng;
   A.lg = P->lg;
   A.h = P->h;
-  A.key = W.key;
+  A.inv_h = 1.0 / P->h;
   A.rank = W.rank;
   A.lstart = W.lstart;
   A.tile = W.scan_tmp;

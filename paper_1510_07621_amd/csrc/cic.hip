@@ -79,8 +79,9 @@ k_deposit_cells(const typename Vec<T>::v4* __restrict__ rec,
   const int b = blockIdx.x;
   const int bz0 = (b % nbz) * BZ, by0 = ((b / nbz) % nby) * BY, bx0 = (b / (nbz * nby)) * BX;
   const auto cell_of = [&](int e) {
-    const int gx = (bx0 - 1 + e / (CY * CZ)) & mask, gy = (by0 - 1 + (e / CZ) % CY) & mask,
-              gz = (bz0 - 1 + e % CZ) & mask;
+    const int row = small_div<CZ>(e), ex = small_div<CY>(row);
+    const int gx = (bx0 - 1 + ex) & mask, gy = (by0 - 1 + row - ex * CY) & mask,
+              gz = (bz0 - 1 + e - row * CZ) & mask;
     return (((gx << lg) | gy) << lg) | gz;
   };
   if (threadIdx.x == 0) nheavy = 0;
@@ -134,6 +135,20 @@ k_deposit_cells(const typename Vec<T>::v4* __restrict__ rec,
   }
 }
 
+// Node gradients of a brick in LDS: FP32 as float4 (a corner is one 16-byte
+// read), FP64 as three arrays.
+template <typename T, int N> struct NodeGrad;
+template <int N> struct NodeGrad<float, N> {
+  float4 g[N];
+  __device__ void put(int i, float x, float y, float z) { g[i] = make_float4(x, y, z, 0.f); }
+  __device__ float4 get(int i) const { return g[i]; }
+};
+template <int N> struct NodeGrad<double, N> {
+  double x[N], y[N], z[N];
+  __device__ void put(int i, double a, double b, double c) { x[i] = a; y[i] = b; z[i] = c; }
+  __device__ double4 get(int i) const { return make_double4(x[i], y[i], z[i], 0.0); }
+};
+
 template <typename T, int BX, int BZ>
 __global__ void __launch_bounds__(kThreads)
 k_interp(const typename Vec<T>::v4* __restrict__ rec, const int32_t* __restrict__ skey,
@@ -142,26 +157,23 @@ k_interp(const typename Vec<T>::v4* __restrict__ rec, const int32_t* __restrict_
          int64_t n, void* __restrict__ force, int force_fp32,
          const typename Vec<T>::v4* __restrict__ acc_pp) {
   constexpr int X1 = BX + 1, Z1 = BZ + 1;        // nodes touched per axis
-  constexpr int X5 = BX + 5, Z5 = BZ + 5;        // with the two-node gradient halo
-  __shared__ T ph[X5 * X5 * Z5];
-  __shared__ T gr[3][X1 * X1 * Z1];
+  using PR = PhiRows<BX, BZ>;
+  __shared__ __align__(16) T ph[PR::kSize];
+  __shared__ __align__(16) NodeGrad<T, X1 * X1 * Z1> gr;
   __shared__ InterpRuns<BX, BZ> R;
   const int mask = ng - 1, nbz = ng / BZ, nbx = ng / BX;
   const int b = blockIdx.x;
   const int bz0 = (b % nbz) * BZ, by0 = ((b / nbz) % nbx) * BX, bx0 = (b / (nbz * nbx)) * BX;
-  for (int i = threadIdx.x; i < X5 * X5 * Z5; i += kThreads) {
-    int nx = i / (X5 * Z5), ny = (i / Z5) % X5, nz = i % Z5;
-    int gx = (bx0 - 2 + nx) & mask, gy = (by0 - 2 + ny) & mask, gz = (bz0 - 2 + nz) & mask;
-    ph[i] = phi[(((int64_t)gx << lg | gy) << lg) | gz];
-  }
+  load_phi<T, BX, BZ>(ph, phi, lg, bx0, by0, bz0);
   load_interp_runs(R, start, lg, bx0, by0, bz0);  // contains __syncthreads
   for (int i = threadIdx.x; i < X1 * X1 * Z1; i += kThreads) {
-    int nx = i / (X1 * Z1), ny = (i / Z1) % X1, nz = i % Z1;
-    int q = ((nx + 2) * X5 + (ny + 2)) * Z5 + (nz + 2);
-    const int sx = X5 * Z5, sy = Z5, sz = 1;
-    gr[0][i] = c1 * (ph[q + sx] - ph[q - sx]) + c2 * (ph[q + 2 * sx] - ph[q - 2 * sx]);
-    gr[1][i] = c1 * (ph[q + sy] - ph[q - sy]) + c2 * (ph[q + 2 * sy] - ph[q - 2 * sy]);
-    gr[2][i] = c1 * (ph[q + sz] - ph[q - sz]) + c2 * (ph[q + 2 * sz] - ph[q - 2 * sz]);
+    const int row = small_div<Z1>(i), nz = i - row * Z1;
+    const int nx = small_div<X1>(row), ny = row - nx * X1;
+    const int q = PR::at(nx, ny, nz);
+    constexpr int sx = PR::kX * PR::kZ, sy = PR::kZ, sz = 1;
+    gr.put(i, c1 * (ph[q + sx] - ph[q - sx]) + c2 * (ph[q + 2 * sx] - ph[q - 2 * sx]),
+           c1 * (ph[q + sy] - ph[q - sy]) + c2 * (ph[q + 2 * sy] - ph[q - 2 * sy]),
+           c1 * (ph[q + sz] - ph[q - sz]) + c2 * (ph[q + 2 * sz] - ph[q - 2 * sz]));
   }
   __syncthreads();
   const int total = R.pre[InterpRuns<BX, BZ>::kR];
@@ -181,9 +193,10 @@ k_interp(const typename Vec<T>::v4* __restrict__ rec, const int32_t* __restrict_
         for (int d = 0; d < 2; ++d) {
           T w = wx[a] * wy[c] * wz[d];
           int q = ((lx + a) * X1 + (ly + c)) * Z1 + (lz + d);
-          ax += w * gr[0][q];
-          ay += w * gr[1][q];
-          az += w * gr[2][q];
+          const typename Vec<T>::v4 g = gr.get(q);
+          ax += w * g.x;
+          ay += w * g.y;
+          az += w * g.z;
         }
     if (acc_out) {
       typename Vec<T>::v4 o;

@@ -158,7 +158,6 @@ size_t carve(p3m_plan* P, unsigned char* base, int64_t n) {
   const size_t real = P->prm.precision == P3M_FP32 ? sizeof(float) : sizeof(double);
   const int64_t nn = n > 0 ? n : 1;
   p3m::Workspace& W = P->ws;
-  W.key = (int32_t*)take(sizeof(int32_t) * nn);
   W.rank = (int32_t*)take(sizeof(int32_t) * nn);
   W.perm = (int32_t*)take(sizeof(int32_t) * nn);
   W.skey = (int32_t*)take(sizeof(int32_t) * nn);

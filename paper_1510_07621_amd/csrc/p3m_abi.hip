@@ -787,7 +787,6 @@ int p3m_plan_create(const p3m_params* prm, int64_t n_max, void* hip_stream, p3m_
 
   hipError_t err = hipGetDevice(&P->device);
   Workspace& W = P->ws;
-  W.key = dev_alloc<int32_t>(nn, err);
   W.rank = dev_alloc<int32_t>(nn, err);
   W.count = dev_alloc<int32_t>(P->ncell + 1, err);
   W.start = dev_alloc<int32_t>(P->ncell + 1, err);
@@ -814,6 +813,7 @@ int p3m_plan_create(const p3m_params* prm, int64_t n_max, void* hip_stream, p3m_
     W.ewald_part = dev_alloc<double>(ewald_part_size(n_max), err);
   }
   if (q.adjoint) {
+    W.key = dev_alloc<int32_t>(nn, err);
     W.lam = dev_alloc<unsigned char>(nn * 4 * real, err);
     W.grid2 = dev_alloc<unsigned char>(P->ncell * real, err);
     W.lam_grid = dev_alloc<unsigned char>(3 * P->ncell * real, err);

@@ -66,7 +66,7 @@ constexpr int64_t kPartialsSlack = 65536;
 // (x, y, z, m) as float4 (FP32 path) or double4 (FP64 path).
 
 struct Workspace {
-  int32_t* key = nullptr;       // [n_max]   cell index per particle (input order)
+  int32_t* key = nullptr;       // [n_max]   cell index per particle (input order; adjoint plans)
   int32_t* rank = nullptr;      // [n_max]   rank inside its cell
   int32_t* count = nullptr;     // [ncell+1] particles per cell
   int32_t* start = nullptr;     // [ncell+1] first sorted slot of each cell; start[ncell] = n
