@@ -337,38 +337,43 @@ hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s) {
 
 // How a call's particles are cut into work items: chunks of `chunk`
 // i-particles, each summed by item_waves waves that share its stencil. A
-// whole item (64 particles, one wave) takes 200 to 400 us from end to end, so
+// whole item (64 particles, one wave) takes 150 to 300 us from end to end, so
 // a set with fewer items than wave slots leaves most of the chip idle and
 // lasts that long whatever its size; a cut item stages its stencil for fewer
-// particles, which costs more in all. Short-range force call (binning
-// included) against whole items, us:
-//   n <= 8192, 16 particles and 8 waves: 4096 on 16^3, FP32 290 -> 47
-//   n <= 65536, 4 waves and 32 particles (FP64, two i-particles a lane, 16):
-//     32768 on 32^3, FP32 332 -> 93, FP64 484 -> 179; adjoint FP32 419 -> 140
-//   n <= 393216, 2 waves and 32: 64^3 on 64^3, FP32 492 -> 395, force and
-//     adjoint FP64 2998 -> 2492 (80^3: 2 waves and 1 even)
-//   larger sets, 32 particles: their last items end sooner and their boxes
-//     clip more. Clustered 2M on 128^3: FP32 2971 -> 2875, adjoint 4722 ->
-//     4454; FP64 1M 2344 -> 2181, but a 128^3 lattice 6008 -> 6189, and at
-//     16.7M particles FP32 41.6 -> 43.1 ms: whole items above 3 2^20 (FP32)
-//     and 3 2^19 (FP64) particles.
+// particles, which costs more in all. Short-range calls, binning included, us,
+// as (chunk, waves):
+//   n <= 8192, (16, 8): 4096 on 16^3, FP32 (64, 1) 290, (16, 4) 44, (16, 8)
+//     39; FP64 adjoint (16, 4) 81, (16, 8) 72
+//   n <= 24576, (16, 4): 16000 on 16^3, FP32 (32, 4) 141, (16, 4) 102, (16, 8)
+//     120; FP64 274, 192, 202
+//   n <= 65536, (32, 4), FP64 (16, 4): 32768 on 32^3, FP32 (32, 2) 117, (32, 4)
+//     84, (16, 4) 87; FP64 (32, 4) 152, (16, 4) 150, adjoint 242, 221
+//   n <= 3 2^17, (32, 2), FP64 (32, 4): 64^3 on 64^3, FP32 (32, 1) 405, (32, 2)
+//     372, (32, 4) 379; FP64 (32, 2) 829, (32, 4) 791, adjoint 1303, 1245
+//   n <= 3 2^18, (32, 2): 80^3 on 64^3, FP32 (32, 1) 1083, (32, 2) 1056; FP64
+//     2620, 2526
+//   n <= 3 2^20, (32, 1): the last items end sooner and their boxes clip more:
+//     2M clustered on 128^3 FP32 (64, 1) 2887, (32, 1) 2761, FP64 6844, 6426;
+//     128^3 lattice 2402, 2290 and 5618, 5584
+//   above, (64, 1): 16.7M clustered FP32, both sides: 41.6 against 43.1 ms
 // Groups that are sparse (under 16 particles on average) have one item each,
-// enough of them to fill the chip: splitting those measured slower (FP32
-// 200001 on 128^3: 2 waves 304 -> 328 us).
+// enough of them to fill the chip: sharing those measured slower (FP32 300007
+// on 128^3: (32, 1) 279, (32, 2) 302).
 static void pair_split(p3m_plan* P, int64_t n) {
   const bool f64 = P->prm.precision == P3M_FP64;
   P->item_waves = 1;
-  P->chunk = n <= (int64_t{3} << (f64 ? 19 : 20)) ? 32 : kChunk;
-  if (n >= 16 * P->ngroup) {
-    if (n <= 8192) {
-      P->item_waves = 8;
-      P->chunk = 16;
-    } else if (n <= 65536) {
-      P->item_waves = 4;
-      if (f64) P->chunk = 16;
-    } else if (n <= 393216) {
-      P->item_waves = 2;
-    }
+  P->chunk = n <= int64_t{3} << 20 ? 32 : kChunk;
+  if (n < 16 * P->ngroup) return;
+  if (n <= 8192) {
+    P->item_waves = 8;
+    P->chunk = 16;
+  } else if (n <= 65536) {
+    P->item_waves = 4;
+    if (f64 || n <= 24576) P->chunk = 16;
+  } else if (n <= int64_t{3} << 17) {
+    P->item_waves = f64 ? 4 : 2;
+  } else if (n <= int64_t{3} << 18) {
+    P->item_waves = 2;
   }
 }
 

@@ -23,8 +23,8 @@ def _gpu():
 
 
 # (n, grid): one particle more or less than a chunk, and both sides of the
-# lines at 8192, 65536 and 393216 particles (with at least 16 a group)
-@pytest.mark.parametrize("n,grid", [(15, 16), (17, 16), (1024, 16), (8191, 16), (8193, 16),
+# lines at 8192, 24576, 65536 and 393216 particles (with at least 16 a group)
+@pytest.mark.parametrize("n,grid", [(15, 16), (17, 16), (1024, 16), (8191, 16), (8193, 16), (24577, 16),
                                     (65536, 32), (65537, 32), (393217, 64)])
 @pytest.mark.parametrize("precision,tol,vjp_tol", [("fp64", 1e-12, 1e-9), ("fp32", 1e-5, 1e-4)])
 def test_cut_items_match_the_oracle(n, grid, precision, tol, vjp_tol):
