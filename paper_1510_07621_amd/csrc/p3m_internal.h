@@ -38,6 +38,7 @@ constexpr int kSplitBins = 64;    // pieces of the split-factor tables
 constexpr int kSplitCoef64 = 7;   // coefficients per piece of the FP64 table (degree 6)
 constexpr double kGroupTarget = 64.0;  // mean particles per i-group the plan aims for
 constexpr int kMaxPowerBins = 512;     // shells of the power spectrum
+constexpr int kMaxGrid = 512;          // cells per side of the largest grid
 // Row stride of the half-complex spectrum along kz: the ng/2 + 1 values of a
 // row padded to a multiple of 16, so that every row, and every 8- or
 // 16-column chunk of one, starts on a 64- (FP32) or 128-byte (FP64) boundary.
