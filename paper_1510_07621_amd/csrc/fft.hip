@@ -392,6 +392,178 @@ __device__ __forceinline__ void col_transform(typename Vec<T>::v2* buf, typename
   }
 }
 
+// ---- Passes 1 and 2, and 4 and 5, in one: an x-plane per block ----
+// Small grids wait for launches (a pass of 32^3 takes 4 us from end to end
+// whatever it does), so the z and y passes of an x-plane run in one block where
+// the plane's half spectrum fits half a CU's LDS: rows of ng/2 + 1 values at
+// stride ng/2 + 2. pm_force of 4096 particles on 16^3 went from 43.0 to 34.1 us,
+// of 32768 on 32^3 from 48.9 to 38.4, of 100001 on 64^3 in FP64 from 66.8 to
+// 57.7, of 2097152 on 128^3 in FP32 from 156.3 to 149.4; an FP64 plane of 128^3
+// (137 KB, one block per CU) is slower so, the power spectrum going from 132.6
+// to 135.4 us, and keeps the separate passes. The y transform is decimation in frequency going forward
+// (natural rows in, bit-reversed rows stored) and in time coming back
+// (bit-reversed rows loaded), the z transforms and the split steps as in the
+// separate passes, the latter in place on the pairs (k, ng/2 - k).
+constexpr size_t kPlaneLds = 80 << 10;
+constexpr int kPlaneThreads = 512;
+
+template <typename T2>
+struct PlaneLds {                       // element p of the lines of length M = 2^lgM
+  T2* buf;
+  int lgM, rs;
+  __device__ T2& at(int p) const { return buf[(p >> lgM) * rs + (p & ((1 << lgM) - 1))]; }
+  __device__ T2 operator()(int p) const { return at(p); }
+  __device__ void operator()(int p, T2 v) const { at(p) = v; }
+};
+
+// One level group of the columns' transforms (M1 columns of length 2^lg):
+// LD(p, c) gives row p of column c, ST(p, c, v) takes it back.
+template <typename T, bool DIT, bool INV, typename LD, typename ST>
+__device__ __forceinline__ void plane_group(int M1, int lg, ColGroup lv,
+                                            const typename Vec<T>::v2* tw, LD ld, ST st) {
+  using T2 = typename Vec<T>::v2;
+  const int l0 = lv.l0, g = lv.g, tasks = M1 << (lg - g);
+  for (int q = threadIdx.x; q < tasks; q += blockDim.x) {
+    const int rem = q / M1, c = q - rem * M1;
+    const int j = rem & ((1 << l0) - 1), p0 = ((rem >> l0) << (l0 + g)) + j;
+    T2 x[1 << kGroup];
+#pragma unroll
+    for (int m = 0; m < (1 << kGroup); ++m)
+      if (m < (1 << g)) x[m] = ld(p0 + (m << l0), c);
+    if (DIT) dit_levels<T, INV>(x, g, j, l0, tw, 1 << lg);
+    else dif_levels<T, INV>(x, g, j, l0, tw, 1 << lg);
+#pragma unroll
+    for (int m = 0; m < (1 << kGroup); ++m)
+      if (m < (1 << g)) st(p0 + (m << l0), c, x[m]);
+  }
+}
+
+// Real plane -> half spectrum along z and y. `clear` as in k_fft_z_r2c.
+template <typename T>
+__global__ void __launch_bounds__(kPlaneThreads)
+k_fft_plane_fwd(const T* __restrict__ grid, typename Vec<T>::v2* __restrict__ spec, int ng, int lg,
+                const typename Vec<T>::v2* __restrict__ tw, double* __restrict__ clear,
+                int nclear) {
+  using T2 = typename Vec<T>::v2;
+  extern __shared__ unsigned char smem_raw[];
+  T2* buf = reinterpret_cast<T2*>(smem_raw);
+  if (clear && blockIdx.x == 0)
+    for (int i = threadIdx.x; i < nclear; i += blockDim.x) clear[i] = 0.0;
+  const int M = ng >> 1, lgM = lg - 1, M1 = M + 1, rs = M + 2, Ms = spec_stride(ng);
+  T2* twl = buf + ng * rs;
+  for (int i = threadIdx.x; i < M; i += blockDim.x) twl[i] = tw[i];
+  const T2* in = reinterpret_cast<const T2*>(grid) + (int64_t)blockIdx.x * ng * M;
+  const PlaneLds<T2> lds{buf, lgM, rs};
+  line_group<T, true, false>(ng, M, lgM, 0, min(kGroup, lgM), tw, ng,
+                             [&](int p) { return in[(p & ~(M - 1)) + brev(p & (M - 1), lgM)]; },
+                             lds);
+  __syncthreads();
+  for (int l0 = kGroup; l0 < lgM; l0 += kGroup) {
+    line_group<T, true, false>(ng, M, lgM, l0, min(kGroup, lgM - l0), twl, ng, lds, lds);
+    __syncthreads();
+  }
+  // the split step: X_k = E + w^k O with E = (Z_k + conj Z_{M-k}) / 2,
+  // O = (Z_k - conj Z_{M-k}) / 2i
+  const auto split = [&](T2 zk, T2 zc, int k) {
+    T2 E, O, w, X;
+    E.x = T(0.5) * (zk.x + zc.x); E.y = T(0.5) * (zk.y - zc.y);
+    O.x = T(0.5) * (zk.y + zc.y); O.y = -T(0.5) * (zk.x - zc.x);
+    if (k < M) w = twl[k]; else { w.x = T(-1); w.y = T(0); }
+    const T2 wo = cmul(w, O);
+    X.x = E.x + wo.x; X.y = E.y + wo.y;
+    return X;
+  };
+  const int half = (M >> 1) + 1;
+  for (int i = threadIdx.x; i < ng * half; i += blockDim.x) {
+    const int y = i / half, k = i - y * half;
+    T2* row = buf + y * rs;
+    const T2 a = row[k], b = row[(M - k) & (M - 1)];
+    const T2 xa = split(a, b, k), xb = split(b, a, M - k);
+    row[k] = xa;
+    row[M - k] = xb;
+  }
+  __syncthreads();
+  T2* plane = spec + (int64_t)blockIdx.x * ng * Ms;
+  const auto col = [&](int p, int c) { return buf[p * rs + c]; };
+  const auto put = [&](int p, int c, T2 v) { buf[p * rs + c] = v; };
+  for (int k = col_groups(lg) - 1; k > 0; --k) {
+    plane_group<T, false, false>(M1, lg, col_group_levels(lg, k), twl, col, put);
+    __syncthreads();
+  }
+  plane_group<T, false, false>(M1, lg, col_group_levels(lg, 0), twl, col, [&](int p, int c, T2 v) {
+    plane[(int64_t)brev(p, lg) * Ms + c] = v;
+  });
+}
+
+// Half spectrum -> real plane along y and z (unnormalised inverse).
+template <typename T>
+__global__ void __launch_bounds__(kPlaneThreads)
+k_fft_plane_inv(const typename Vec<T>::v2* __restrict__ spec, T* __restrict__ grid, int ng, int lg,
+                const typename Vec<T>::v2* __restrict__ tw) {
+  using T2 = typename Vec<T>::v2;
+  extern __shared__ unsigned char smem_raw[];
+  T2* buf = reinterpret_cast<T2*>(smem_raw);
+  const int M = ng >> 1, lgM = lg - 1, M1 = M + 1, rs = M + 2, Ms = spec_stride(ng);
+  T2* twl = buf + ng * rs;
+  for (int i = threadIdx.x; i < M; i += blockDim.x) twl[i] = tw[i];
+  const T2* plane = spec + (int64_t)blockIdx.x * ng * Ms;
+  const auto col = [&](int p, int c) { return buf[p * rs + c]; };
+  const auto put = [&](int p, int c, T2 v) { buf[p * rs + c] = v; };
+  plane_group<T, true, true>(
+      M1, lg, col_group_levels(lg, 0), tw,
+      [&](int p, int c) { return plane[(int64_t)brev(p, lg) * Ms + c]; }, put);
+  __syncthreads();
+  for (int k = 1; k < col_groups(lg); ++k) {
+    plane_group<T, true, true>(M1, lg, col_group_levels(lg, k), twl, col, put);
+    __syncthreads();
+  }
+  // E = X_k + conj X_{M-k}, O = (X_k - conj X_{M-k}) conj(w^k), Z = E + i O
+  const auto join = [&](T2 xk, T2 xc, int k) {
+    T2 D, w = twl[k], Z;
+    D.x = xk.x - xc.x; D.y = xk.y + xc.y;
+    w.y = -w.y;
+    const T2 O = cmul(D, w);
+    Z.x = xk.x + xc.x - O.y; Z.y = xk.y - xc.y + O.x;
+    return Z;
+  };
+  const int half = (M >> 1) + 1;
+  for (int i = threadIdx.x; i < ng * half; i += blockDim.x) {
+    const int y = i / half, k = i - y * half;
+    T2* row = buf + y * rs;
+    const T2 a = row[k], b = row[M - k];
+    const T2 za = join(a, b, k);
+    if (k) row[M - k] = join(b, a, M - k);
+    row[k] = za;
+  }
+  __syncthreads();
+  const PlaneLds<T2> lds{buf, lgM, rs};
+  T2* out = reinterpret_cast<T2*>(grid) + (int64_t)blockIdx.x * ng * M;
+  for (int k = 0; k < lgM; k += kGroup) {
+    const int g = min(kGroup, lgM - k), l0 = lgM - k - g;
+    if (l0 > 0) {
+      line_group<T, false, true>(ng, M, lgM, l0, g, twl, ng, lds, lds);
+      __syncthreads();
+    } else {
+      line_group<T, false, true>(ng, M, lgM, l0, g, twl, ng, lds, [&](int p, T2 v) {
+        out[(p & ~(M - 1)) + brev(p & (M - 1), lgM)] = v;
+      });
+    }
+  }
+}
+
+template <typename T>
+size_t plane_lds(int ng) {
+  const int M = ng / 2;
+  return ((size_t)ng * (M + 2) + M) * sizeof(typename Vec<T>::v2);
+}
+
+template <typename T>
+bool plane_fits(int ng) {
+  return plane_lds<T>(ng) <= kPlaneLds;
+}
+
+int plane_threads(int ng) { return ng < 64 ? 256 : kPlaneThreads; }
+
 // Pass 2 / 4: complex transform along y for one x-plane and a chunk of kc
 // kz-columns.
 template <typename T, bool INV>
@@ -642,6 +814,14 @@ hipError_t launch_fft_poisson(p3m_plan* P) {
   const T* etab = (const T*)W.gtab;
   T gconst = (T)(-4.0 * M_PI * P->prm.G / ((double)ng * ng * ng));
 
+  if (plane_fits<T>(ng)) {
+    const int threads = plane_threads(ng);
+    k_fft_plane_fwd<T><<<ng, threads, plane_lds<T>(ng), s>>>(grid, spec, ng, lg, tw, nullptr, 0);
+    k_fft_x_green<T><<<ng * nchunk, kThreads, lds_c, s>>>(spec, ng, lg, kc, tw, etab,
+                                                          etab + ng, gconst);
+    k_fft_plane_inv<T><<<ng, threads, plane_lds<T>(ng), s>>>(spec, grid, ng, lg, tw);
+    return hipGetLastError();
+  }
   k_fft_z_r2c<T><<<blocks_z, kThreads, lds_z, s>>>(grid, spec, ng, lg, nl, tw, nullptr, 0);
   k_fft_y<T, false><<<ng * nchunk, kThreads, lds_c, s>>>(spec, ng, lg, kc, tw);
   k_fft_x_green<T><<<ng * nchunk, kThreads, lds_c, s>>>(spec, ng, lg, kc, tw, etab,
@@ -669,9 +849,14 @@ hipError_t launch_power_spectrum(p3m_plan* P, int nbins, double r_tophat, double
   if (kc < 1) kc = 1;
   size_t lds_c = (size_t)(padded(kc * ng) + M) * sizeof(T2);
   unsigned nchunk = (unsigned)((M1 + kc - 1) / kc);
-  k_fft_z_r2c<T><<<blocks_z, kThreads, lds_z, s>>>((const T*)W.grid, spec, ng, lg, nl, tw,
-                                                   W.power_acc, 3 * nbins + 2);
-  k_fft_y<T, false><<<ng * nchunk, kThreads, lds_c, s>>>(spec, ng, lg, kc, tw);
+  if (plane_fits<T>(ng)) {
+    k_fft_plane_fwd<T><<<ng, plane_threads(ng), plane_lds<T>(ng), s>>>(
+        (const T*)W.grid, spec, ng, lg, tw, W.power_acc, 3 * nbins + 2);
+  } else {
+    k_fft_z_r2c<T><<<blocks_z, kThreads, lds_z, s>>>((const T*)W.grid, spec, ng, lg, nl, tw,
+                                                     W.power_acc, 3 * nbins + 2);
+    k_fft_y<T, false><<<ng * nchunk, kThreads, lds_c, s>>>(spec, ng, lg, kc, tw);
+  }
   k_fft_x_power<T><<<ng * nchunk, kThreads, lds_c, s>>>(
       spec, ng, lg, kc, tw, P->prm.deconv_power != 0 ? 1 : 0, nbins,
       2.0 * M_PI / P->prm.box * r_tophat, W.power_acc);
