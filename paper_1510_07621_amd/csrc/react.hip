@@ -217,6 +217,14 @@ k_scan64_add(long long* __restrict__ out, int64_t len, const long long* __restri
 
 // ---- the gather ----
 
+// Segments whose tables a particle reads together in the gather, before the
+// partials of either: the chain of loads to the first partial is then walked
+// half as often. 16777216 particles of a Plummer sphere on 256^3 in FP32, where
+// the gather fetches 9.7 GB of partials in runs of a cell's particles: 5.55 ->
+// 4.89 ms (2.0 TB/s); four at a time 5.15 (registers), one record per group for
+// its three tables 4.87, blocks contiguous per XCD 5.75.
+constexpr int kBatch = 2;
+
 template <typename T>
 struct GatherArgs {
   const typename Vec<T>::v4* __restrict__ rec;   // sorted records (mass in w)
@@ -303,29 +311,37 @@ k_react_gather(GatherArgs<T> A) {
     //    the cell when the cell's z offset from that group lies in it
     const int key = ((cx & (G - 1)) << lgG) | (cy & (G - 1));
     const int kb = A.pboff[key], ke = A.pboff[key + 1];
-    for (int k = kb; k < ke; ++k) {
-      const int4 p = A.pbrows[k];
-      const int oz = p.y >> lgG;
-      const int zoff = (oz << lgG) + (cz & (G - 1));
-      if (zoff < p.y || zoff > p.z) continue;
-      const int dx = (int)(short)(p.x & 0xffff), dy = p.x >> 16;
-      const int64_t g = group_at(gx, gy, gz, -(dx >> lgG), -(dy >> lgG), -oz, lgd);
-      const int ntot = A.gntot[g];
-      if (ntot <= kDenseMin) continue;         // sparse: wrote no partials
-      const int K = (ntot + kChunk - 1) / kChunk;
-      const int32_t* ro = A.rowoff + g * np1;
-      const int L = ro[A.npos];
-      // the segment's cells below the particle's (same column, same group
-      // of cells along z), then the particle's place in its cell
-      const long long q = ro[p.w] + (s - A.start[colbase + cz - (zoff - p.y)]);
-      const long long gb = A.gbase[g];
+    for (int k0 = kb; k0 < ke; k0 += kBatch) {
+      int K[kBatch], L[kBatch], nt[kBatch];
+      long long at[kBatch];
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
+        const int4 p = A.pbrows[min(k0 + u, ke - 1)];
+        const int oz = p.y >> lgG;
+        const int zoff = (oz << lgG) + (cz & (G - 1));
+        const int dx = (int)(short)(p.x & 0xffff), dy = p.x >> 16;
+        const int64_t g = group_at(gx, gy, gz, -(dx >> lgG), -(dy >> lgG), -oz, lgd);
+        nt[u] = A.gntot[g];
+        const int32_t* ro = A.rowoff + g * np1;
+        L[u] = ro[A.npos];
+        // the segment's cells below the particle's (same column, same group
+        // of cells along z), then the particle's place in its cell; a segment
+        // without the cell counts from the cell itself, unused
+        const int below = min(max(zoff - p.y, 0), cz & (G - 1));
+        at[u] = A.gbase[g] + ro[p.w] + (s - A.start[colbase + cz - below]);
+        const bool hit = k0 + u < ke && zoff >= p.y && zoff <= p.z && nt[u] > kDenseMin;
+        K[u] = hit ? (nt[u] + kChunk - 1) / kChunk : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u) {
 #pragma unroll 4
-      for (int ch = 0; ch < K; ++ch) {
-        const long long idx =
-            min(item_base(gb, ntot, L, ch) + max(ntot - kChunk * (ch + 1), 0) + q, last);
-        sx += pr[3 * idx];
-        sy += pr[3 * idx + 1];
-        sz += pr[3 * idx + 2];
+        for (int ch = 0; ch < K[u]; ++ch) {
+          const long long idx = min(
+              item_base(at[u], nt[u], L[u], ch) + max(nt[u] - kChunk * (ch + 1), 0), last);
+          sx += pr[3 * idx];
+          sy += pr[3 * idx + 1];
+          sz += pr[3 * idx + 2];
+        }
       }
     }
     const double f = UM ? A.rscale * (double)rs.w : A.rscale;
