@@ -81,9 +81,9 @@ typedef struct p3m_params {
                              keeps the reactions as partials, of which the plan
                              holds pair_partials per particle (80 suits strongly
                              clustered sets); a call that needs more falls back
-                             to both sides, and so do forces on up to 3 2^20 and
-                             adjoints of up to 3 2^17 particles, where both sides
-                             are faster. Pays on large clustered sets (256^3
+                             to both sides, and so do FP64 forces, FP32 forces on
+                             up to 3 2^20 and adjoints of up to 5 2^19 particles,
+                             where both sides are faster. Pays on large clustered sets (256^3
                              Plummer mix: -11 %), not on smooth ones            */
 } p3m_params;
 
@@ -104,8 +104,8 @@ int p3m_params_default(p3m_params* out, int32_t grid_n, double box);
  * ewald_gridsize not 0 or even in 8..512,
  * n_max < 0 or n_max >= 2^31; ERANGE when r_c >= box/2), then allocates the
  * workspace (with adjoint = 1 also that of the VJP calls: one more real grid,
- * three cotangent grids and a sorted cotangent array; with pair_partials > 0
- * the reaction partials, pair_partials n_max + 65536 of 3 reals each (at 80:
+ * three cotangent grids and a sorted cotangent array; with pair_partials > 0,
+ * in FP32 or with adjoint = 1, the reaction partials, pair_partials n_max + 65536 of 3 reals each (at 80:
  * 0.96 KB (FP32) or 1.9 KB (FP64) per particle), plus per-group offsets; if
  * that allocation fails the plan evaluates every pair from both sides)
  * (ENOMEM on failure; nothing is leaked). *out is set only on success.

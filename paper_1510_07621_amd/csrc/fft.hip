@@ -12,6 +12,8 @@
 //   3. x, complex forward, multiply by the Green's function, x inverse (fused);
 //   4. y, complex inverse;
 //   5. z, complex -> real (the split step in reverse, then ng/2 complex inverse).
+// Where an x-plane's half spectrum fits half a CU's LDS, passes 1 and 2 are one
+// launch and 4 and 5 another (k_fft_plane_fwd, k_fft_plane_inv), a plane per block.
 // Transforms are radix-2: decimation in time (bit-reversed input, natural
 // output) forward and decimation in frequency (natural input, bit-reversed
 // output) inverse, so no pass needs a separate reordering step; three levels

@@ -105,10 +105,11 @@ void begin_call(p3m_plan* P) {
 
 enum class Part { kP3M, kPM, kPP };
 
-// A one-sided plan evaluates small sets from both sides all the same (see
-// kOneSidedMin).
+// A one-sided plan evaluates small sets, and FP64 forces, from both sides all
+// the same (see kOneSidedMin).
 bool one_sided_call(const p3m_plan* P, int64_t n, bool vjp) {
-  return P->rcap > 0 && n > (vjp ? kOneSidedVjpMin : kOneSidedMin);
+  if (P->rcap <= 0) return false;
+  return vjp ? n > kOneSidedVjpMin : P->prm.precision == P3M_FP32 && n > kOneSidedMin;
 }
 
 // Launches that take the plan's stream enqueue on `s` while this is alive.
@@ -819,8 +820,10 @@ int p3m_plan_create(const p3m_params* prm, int64_t n_max, void* hip_stream, p3m_
     W.lam_grid = dev_alloc<unsigned char>(3 * P->ncell * real, err);
   }
   // the one-sided pair sum: half stencil, per-group offsets, partials; if the
-  // partials do not fit, the plan sums every pair from both sides
-  if (err == hipSuccess && q.pair_partials > 0 && P->npos > 0) {
+  // partials do not fit, the plan sums every pair from both sides (an FP64
+  // plan's forces do in any case: only its adjoints take partials)
+  if (err == hipSuccess && q.pair_partials > 0 && P->npos > 0 &&
+      (q.precision == P3M_FP32 || q.adjoint)) {
     W.segrows = dev_alloc<int4>(P->nseg, err);
     W.prows = dev_alloc<int4>(P->npos, err);
     W.pbrows = dev_alloc<int4>(P->npos, err);

@@ -28,11 +28,15 @@ constexpr int kMinChunk = 16;     // the smallest chunk that small sets are cut 
 // also in a one-sided plan: the two-sided sum's items can be cut as small as
 // the set asks for (pair_split), the one-sided sum's follow its partials.
 // Clustered sets, two- against one-sided, force call in ms: 32769 on 32^3
-// FP32 0.13, 0.36; 500001 on 64^3 FP32 1.21, 1.32; 2M on 128^3 FP32 2.97,
-// 3.48, FP64 7.3, 9.2; 16.7M on 256^3 FP32 45.2, 40.2. Adjoint: 262145 on
-// 64^3 FP32 0.72, 0.92, FP64 1.66, 2.01; 500001 on 64^3 FP64 4.95, 4.75.
+// FP32 0.11, 0.31; 500001 on 64^3 FP32 1.15, 1.22; 2M on 128^3 FP32 2.89,
+// 3.23; 3M 5.76, 5.88; 4M 9.29, 8.75; 16.7M on 256^3 43.7, 37.8. FP64, whose
+// partials are twice as long, never gained: 2M on 128^3 6.6, 8.4; 4M 23.1,
+// 26.1; 8M 75.2, 86.7; 8M on 256^3 28.7, 30.7; 16.7M 109.8, 112.3; its forces
+// are two-sided. Adjoint: 500001 on 64^3 FP32 1.70, 1.87, FP64 4.03, 4.33; 2M
+// on 128^3 4.61, 4.93 and 10.94, 11.02; 2.3M 5.74, 6.00 and 13.96, 13.72; 3M
+// 9.10, 8.93 and 22.4, 21.0.
 constexpr int64_t kOneSidedMin = int64_t{3} << 20;
-constexpr int64_t kOneSidedVjpMin = int64_t{3} << 17;
+constexpr int64_t kOneSidedVjpMin = int64_t{5} << 19;
 constexpr int kXcds = 8;          // accelerator complex dies of an MI355X (one L2 each)
 constexpr int kSplitBins = 64;    // pieces of the split-factor tables
 constexpr int kSplitCoef64 = 7;   // coefficients per piece of the FP64 table (degree 6)
@@ -50,9 +54,9 @@ __host__ __device__ inline int spec_stride(int ng) { return ((ng >> 1) + 1 + 15)
 constexpr int64_t kPartialsPerParticle = 80;
 // A group is dense (pairs with other dense groups evaluated once) above
 // this many particles. Measured on the clustered 256^3 set (FP32 pair
-// kernel + gather per force call, partials stored by record): above 48
-// particles 33.1 + 5.0 ms, above 40 32.8 + 5.2, above 32 32.5 + 5.6, above
-// 24 32.4 + 6.2 ms: fewer evaluations, more partials to gather; the sum is
+// kernel + gather per force call): above 48 particles 31.5 + 4.3 ms, above 32
+// 31.0 + 4.9, above 24 30.6 + 5.4, above 16 30.3 + 6.5 ms: fewer evaluations,
+// more partials to gather; the sum is
 // flat from 48 down to 32, which has the faster pair kernel. On a displaced
 // lattice at one particle per cell (64 per group) most groups are then
 // dense and the one-sided sum does not pay there, which is why it is a plan

@@ -1308,19 +1308,21 @@ hipError_t launch_pair_kernel(p3m_plan* P, const PairArgs<T>& A, bool uniform_ma
   const unsigned grid = pair_grid(P, A.n);
   const bool tab = (sizeof(T) == 4 ? P->tab_var : P->tab64_var) == 1;
   // table over the softened distance (1) or over r (0)
-  if (half) {
-    if (tab) {
-      if (uniform_mass)
-        k_pairs<T, false, true, 1, VJP, true><<<grid, 64, 0, P->stream>>>(A);
-      else
-        k_pairs<T, false, false, 1, VJP, true><<<grid, 64, 0, P->stream>>>(A);
-    } else {
-      if (uniform_mass)
-        k_pairs<T, false, true, 0, VJP, true><<<grid, 64, 0, P->stream>>>(A);
-      else
-        k_pairs<T, false, false, 0, VJP, true><<<grid, 64, 0, P->stream>>>(A);
+  if constexpr (sizeof(T) == 4 || VJP) {     // (FP64 forces: two-sided, see kOneSidedMin)
+    if (half) {
+      if (tab) {
+        if (uniform_mass)
+          k_pairs<T, false, true, 1, VJP, true><<<grid, 64, 0, P->stream>>>(A);
+        else
+          k_pairs<T, false, false, 1, VJP, true><<<grid, 64, 0, P->stream>>>(A);
+      } else {
+        if (uniform_mass)
+          k_pairs<T, false, true, 0, VJP, true><<<grid, 64, 0, P->stream>>>(A);
+        else
+          k_pairs<T, false, false, 0, VJP, true><<<grid, 64, 0, P->stream>>>(A);
+      }
+      return hipGetLastError();
     }
-    return hipGetLastError();
   }
   switch (P->item_waves) {
     case 2: return launch_two_sided<T, VJP, 2>(P, A, uniform_mass, tab);
@@ -1334,11 +1336,13 @@ template <typename T>
 hipError_t launch_pairs(p3m_plan* P, int64_t n, bool add_pm, void* force_out, int force_fp32,
                         bool uniform_mass, void* acc_out) {
   PairArgs<T> A = make_args<T>(P, n);
-  if (P->one_sided && !add_pm) {
-    // one-sided sum: the sorted action into ws.acc_pm; launch_pair_gather
-    // then adds the reactions and writes the result
-    A.acc_out = (typename Vec<T>::v4*)P->ws.acc_pm;
-    return launch_pair_kernel<T, false>(P, A, uniform_mass, true);
+  if constexpr (sizeof(T) == 4) {
+    if (P->one_sided && !add_pm) {
+      // one-sided sum: the sorted action into ws.acc_pm; launch_pair_gather
+      // then adds the reactions and writes the result
+      A.acc_out = (typename Vec<T>::v4*)P->ws.acc_pm;
+      return launch_pair_kernel<T, false>(P, A, uniform_mass, true);
+    }
   }
   A.acc_pm = add_pm ? (const typename Vec<T>::v4*)P->ws.acc_pm : nullptr;
   A.acc_out = (typename Vec<T>::v4*)acc_out;

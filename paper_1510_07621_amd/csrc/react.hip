@@ -220,8 +220,8 @@ k_scan64_add(long long* __restrict__ out, int64_t len, const long long* __restri
 // Segments whose tables a particle reads together in the gather, before the
 // partials of either: the chain of loads to the first partial is then walked
 // half as often. 16777216 particles of a Plummer sphere on 256^3 in FP32, where
-// the gather fetches 9.7 GB of partials in runs of a cell's particles: 5.55 ->
-// 4.89 ms (2.0 TB/s); four at a time 5.15 (registers), one record per group for
+// the gather fetches 20 GB, the partials in runs of a cell's particles: 5.55 ->
+// 4.89 ms (4.1 TB/s); four at a time 5.15 (registers), one record per group for
 // its three tables 4.87, blocks contiguous per XCD 5.75.
 constexpr int kBatch = 2;
 

@@ -46,7 +46,8 @@ def test_cut_items_match_the_oracle(n, grid, precision, tol, vjp_tol):
 
 
 @pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32", 1e-5)])
-@pytest.mark.parametrize("kind,n,grid", [("force", 3200001, 128), ("vjp", 400001, 64)])
+@pytest.mark.parametrize("kind,n,grid", [("force", 3200001, 128), ("vjp", 400001, 64),
+                                         ("vjp", 2700001, 128)])
 def test_one_sided_above_its_line(precision, tol, kind, n, grid):
     """Above the line the one-sided sum, with enough partials and with too few
     (the call then falls back on the device), equals the two-sided sum: dense
