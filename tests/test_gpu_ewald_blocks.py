@@ -44,3 +44,24 @@ def test_block_sum_equals_the_plain_sum(grid, E, kind, n):
     assert ok.sum() >= n // 4
     err = np.linalg.norm((got - want)[:, ok]) / np.linalg.norm(want[:, ok])
     assert err <= 1e-12, err
+
+
+@pytest.mark.parametrize("n", [65536, 65537])
+def test_both_sides_of_the_block_sums_line(n):
+    """Up to 65536 particles by blocks, above from both sides: sampled
+    particles against the plain sum, to n rounding errors of the terms."""
+    require_gpu()
+    pos = ics.uniform(n, 1.0, seed=n)
+    m = np.random.default_rng(n).uniform(0.5, 1.5, n) / n
+    eps = 1e-3
+    tg = np.array([0, 1, 511, 512, 40000, n - 2, n - 1])
+    d = pos[:, tg, None] - pos[:, None, :]
+    d -= np.rint(d)
+    with plan(32, n, "fp64", softening=eps, ewald_gridsize=16) as P:
+        got = host(P.pp_ewald_force(dev(pos), dev(m)))[:, tg]
+        c = host(P.ewald_correction(dev(np.ascontiguousarray(d.reshape(3, -1))))).reshape(d.shape)
+    r2 = (d * d).sum(0)
+    pair = np.where(r2 > 0, d / np.where(r2 > 0, r2 + eps * eps, 1.0) ** 1.5 + c, 0.0) * m
+    size = m[tg] * np.sqrt((pair * pair).sum(0)).sum(1)
+    err = np.sqrt(((got + m[tg] * pair.sum(2)) ** 2).sum(0))
+    assert (err <= n * 2.0 ** -53 * size).all(), err / size
