@@ -266,8 +266,14 @@ k_bin_finish(FinishArgs<T> A) {
     r.z = (T)(z - cz * A.h);
     r.w = (T)(A.mass ? A.mass[i] : A.mass_scalar);
     A.rec[dst] = r;
-    A.perm[dst] = (int32_t)i;
-    A.skey[dst] = c;
+    // (a deposit reads neither: for particles in random order each of these
+    // stores is a cache line of its own. Power spectrum of 16.7M clustered
+    // particles on 256^3 2408 -> 1926 us, 2M on 128^3 in FP64 323 -> 272, of a
+    // 128^3 lattice, whose lines are shared, 135.6 -> 133.5)
+    if (A.perm) {
+      A.perm[dst] = (int32_t)i;
+      A.skey[dst] = c;
+    }
     return;
   }
   b -= A.scatter_blocks;
@@ -396,7 +402,7 @@ static hipError_t launch_finish(p3m_plan* P, int64_t n, const double* pos, const
   A.nt = scan_tiles(P->ncell);
   A.ncell = P->ncell;
   A.start = W.start;
-  A.perm = W.perm;
+  A.perm = items == Items::kRecords ? nullptr : W.perm;
   A.skey = W.skey;
   A.rec = (typename Vec<T>::v4*)W.rec;
   A.scatter_blocks = (int)blocks_for(n, kThreads);
@@ -407,7 +413,7 @@ static hipError_t launch_finish(p3m_plan* P, int64_t n, const double* pos, const
   A.chunk = P->chunk;
   A.items = W.items;
   const unsigned blocks = (unsigned)(A.scatter_blocks + A.start_blocks) +
-                          (items == Items::kNone ? 0 : blocks_for(P->ngroup, kThreads));
+                          (items <= Items::kNone ? 0 : blocks_for(P->ngroup, kThreads));
   if (A.nt <= kThreads)
     k_bin_finish<T, 1><<<blocks, kThreads, 0, P->stream>>>(A);
   else if (A.nt <= kFuseTiles)

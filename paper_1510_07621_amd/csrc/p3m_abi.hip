@@ -954,7 +954,7 @@ int p3m_power_spectrum(p3m_plan* P, int64_t n, const double* pos, const double* 
   hipError_t e;
   {
     StageTimer t(P, P3M_STAGE_BIN);
-    if ((e = launch_bin(P, n, pos, mass, mass_scalar, Items::kNone)) != hipSuccess)
+    if ((e = launch_bin(P, n, pos, mass, mass_scalar, Items::kRecords)) != hipSuccess)
       return status_of(e);
   }
   const bool f32 = P->prm.precision == P3M_FP32;

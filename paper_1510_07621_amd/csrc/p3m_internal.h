@@ -167,9 +167,11 @@ namespace p3m {
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 int scan_tiles(int64_t ncell);        // tiles of the cell counts' scan
 
-// The pair loop's work list: none, in chunks of kChunk with one wave each
-// (whole), or cut as pair_split says.
-enum class Items { kNone, kWhole, kCut };
+// What a binning leaves: the sorted records and the cells' first slots alone (a
+// deposit's input); with them the slots' input index and cell (kNone); or also
+// the pair loop's work list, in chunks of kChunk with one wave each (whole) or
+// cut as pair_split says.
+enum class Items { kRecords, kNone, kWhole, kCut };
 hipError_t launch_bin(p3m_plan* P, int64_t n, const double* pos, const double* mass,
                       double mass_scalar, Items items);
 
