@@ -65,3 +65,24 @@ def test_both_sides_of_the_block_sums_line(n):
     size = m[tg] * np.sqrt((pair * pair).sum(0)).sum(1)
     err = np.sqrt(((got + m[tg] * pair.sum(2)) ** 2).sum(0))
     assert (err <= n * 2.0 ** -53 * size).all(), err / size
+
+
+@pytest.mark.parametrize("n", [1, 3, 65, 700])
+def test_particles_next_to_the_origin(n):
+    """Without softening, a particle next to the origin but not on it: the
+    places past the last particle, which the blocks fill with no mass at the
+    origin, add nothing to it (its weight with them would overflow)."""
+    require_gpu()
+    pos = ics.uniform(n, 1.0, seed=n)
+    pos[:, 0] = (1e-120, 0.0, 1e-130)
+    m = np.random.default_rng(n).uniform(0.5, 1.5, n) / n
+    d = pos[:, :, None] - pos[:, None, :]
+    d -= np.rint(d)
+    with plan(16, n, "fp64", softening=0.0, ewald_gridsize=16) as P:
+        got = host(P.pp_ewald_force(dev(pos), dev(m)))
+        c = host(P.ewald_correction(dev(d.reshape(3, -1)))).reshape(3, n, n)
+    r2 = (d * d).sum(0)
+    pair = np.where(r2 > 0, d / np.where(r2 > 0, r2, 1.0) ** 1.5 + c, 0.0)
+    want = -m * (pair * m).sum(2)
+    assert np.isfinite(got).all(), got[:, ~np.isfinite(got).all(axis=0)]
+    assert np.linalg.norm(got - want) <= 1e-12 * np.linalg.norm(want)
