@@ -114,6 +114,14 @@ int p3m_params_default(p3m_params* out, int32_t grid_n, double box);
 int p3m_plan_create(const p3m_params* params, int64_t n_max, void* hip_stream,
                     p3m_plan** out);
 
+/* p3m_plan_create with the line of the one-sided pair sum moved: in a plan
+ * with pair_partials > 0, FP32 forces and adjoints of more than `above`
+ * particles evaluate pairs of dense groups once, whether or not that is
+ * faster (above = -1: the library's own lines, as p3m_plan_create; EINVAL
+ * below -1). FP64 forces are evaluated from both sides in any plan. */
+int p3m_plan_create_one_sided(const p3m_params* params, int64_t n_max, int64_t above,
+                              void* hip_stream, p3m_plan** out);
+
 /* Release the plan and its workspace (the counterpart of p3m_plan_create).
  * Synchronises the plan's stream first. A null plan is a no-op returning
  * P3M_OK. */

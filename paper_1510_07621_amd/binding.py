@@ -56,6 +56,8 @@ def _load():
         "p3m_params_default": (ctypes.c_int, [ctypes.POINTER(P3MParams), i32, dbl]),
         "p3m_plan_create": (ctypes.c_int, [ctypes.POINTER(P3MParams), i64, vp,
                                            ctypes.POINTER(vp)]),
+        "p3m_plan_create_one_sided": (ctypes.c_int, [ctypes.POINTER(P3MParams), i64, i64, vp,
+                                                     ctypes.POINTER(vp)]),
         "p3m_plan_destroy": (ctypes.c_int, [vp]),
         "p3m_plan_set_stream": (ctypes.c_int, [vp, vp]),
         "p3m_force": (ctypes.c_int, [vp, i64, vp, vp, dbl, vp, i32]),
@@ -296,15 +298,18 @@ def pp_force_noalloc(params: Params, pos, mass=None, out=None, fp32_out=False):
 
 
 class Plan:
-    """Owns a libp3m plan (workspace for up to ``n_max`` particles)."""
+    """Owns a libp3m plan (workspace for up to ``n_max`` particles).
+    ``one_sided_above`` moves the line of the one-sided pair sum
+    (p3m_plan_create_one_sided; default: the library's own)."""
 
-    def __init__(self, params: Params, n_max: int, stream=None):
+    def __init__(self, params: Params, n_max: int, stream=None, one_sided_above: int = -1):
         self.params = params
         self.n_max = int(n_max)
         c = params.to_c()
         h = ctypes.c_void_p()
-        _check(_lib.p3m_plan_create(ctypes.byref(c), self.n_max, _stream_ptr(stream),
-                                    ctypes.byref(h)), "p3m_plan_create")
+        _check(_lib.p3m_plan_create_one_sided(ctypes.byref(c), self.n_max, int(one_sided_above),
+                                              _stream_ptr(stream), ctypes.byref(h)),
+               "p3m_plan_create")
         self._h = h
 
     def close(self):

@@ -108,8 +108,9 @@ enum class Part { kP3M, kPM, kPP };
 // A one-sided plan evaluates small sets, and FP64 forces, from both sides all
 // the same (see kOneSidedMin).
 bool one_sided_call(const p3m_plan* P, int64_t n, bool vjp) {
-  if (P->rcap <= 0) return false;
-  return vjp ? n > kOneSidedVjpMin : P->prm.precision == P3M_FP32 && n > kOneSidedMin;
+  if (P->rcap <= 0 || (!vjp && P->prm.precision != P3M_FP32)) return false;
+  if (P->one_sided_above >= 0) return n > P->one_sided_above;
+  return n > (vjp ? kOneSidedVjpMin : kOneSidedMin);
 }
 
 // Launches that take the plan's stream enqueue on `s` while this is alive.
@@ -772,10 +773,16 @@ int p3m_params_default(p3m_params* out, int32_t grid_n, double box) {
 }
 
 int p3m_plan_create(const p3m_params* prm, int64_t n_max, void* hip_stream, p3m_plan** out) {
-  if (!prm || !out) return P3M_EINVAL;
+  return p3m_plan_create_one_sided(prm, n_max, -1, hip_stream, out);
+}
+
+int p3m_plan_create_one_sided(const p3m_params* prm, int64_t n_max, int64_t above,
+                              void* hip_stream, p3m_plan** out) {
+  if (!prm || !out || above < -1) return P3M_EINVAL;
   const p3m_params& q = *prm;
   p3m_plan* P = new (std::nothrow) p3m_plan;
   if (!P) return P3M_ENOMEM;
+  P->one_sided_above = above;
   const int st = p3m::plan_geometry(q, n_max, P);
   if (st != P3M_OK) {
     delete P;

@@ -141,6 +141,8 @@ struct p3m_plan {
   int nrows = 0;
   int nseg = 0, npos = 0;       // stencil segments, and the positive ones
   int64_t rcap = 0;             // reaction partials the plan holds (0: two-sided sum only)
+  int64_t one_sided_above = -1; // one-sided calls on more particles than this (-1: the
+                                // library's lines, kOneSidedMin and kOneSidedVjpMin)
   int64_t max_items = 0;
   // the pair loop's work items of the call in progress (pair_split)
   int chunk = p3m::kChunk;      // i-particles per item

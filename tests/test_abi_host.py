@@ -85,6 +85,18 @@ def test_plan_create_rejects_bad_sizes_and_nulls(b):
     assert b._lib.p3m_plan_create(ctypes.byref(bad), 4, None, ctypes.byref(h)) == -1
 
 
+def test_plan_create_one_sided_rejects_what_plan_create_does(b):
+    p, h = b.Params(grid_n=32, pair_partials=80).to_c(), ctypes.c_void_p()
+    make = b._lib.p3m_plan_create_one_sided
+    assert make(ctypes.byref(p), 4, -2, None, ctypes.byref(h)) == -1
+    assert make(None, 4, 0, None, ctypes.byref(h)) == -1
+    assert make(ctypes.byref(p), 4, 0, None, None) == -1
+    assert make(ctypes.byref(p), -1, 0, None, ctypes.byref(h)) == -1
+    p.grid_n = 100
+    assert make(ctypes.byref(p), 4, 0, None, ctypes.byref(h)) == -1
+    assert not h.value
+
+
 def test_calls_on_null_plan_and_bad_arguments(b):
     L = b._lib
     for fn in (L.p3m_force, L.pm_force, L.pp_force):
