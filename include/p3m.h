@@ -105,9 +105,10 @@ int p3m_params_default(p3m_params* out, int32_t grid_n, double box);
  * n_max < 0 or n_max >= 2^31; ERANGE when r_c >= box/2), then allocates the
  * workspace (with adjoint = 1 also that of the VJP calls: one more real grid,
  * three cotangent grids and a sorted cotangent array; with pair_partials > 0,
- * in FP32 or with adjoint = 1, the reaction partials, pair_partials n_max + 65536 of 3 reals each (at 80:
- * 0.96 KB (FP32) or 1.9 KB (FP64) per particle), plus per-group offsets; if
- * that allocation fails the plan evaluates every pair from both sides)
+ * if a call on n_max particles may evaluate pairs once, the reaction
+ * partials, pair_partials n_max + 65536 of 3 reals each (at 80: 0.96 KB (FP32)
+ * or 1.9 KB (FP64) per particle), plus per-group offsets; if that allocation
+ * fails the plan evaluates every pair from both sides)
  * (ENOMEM on failure; nothing is leaked). *out is set only on success.
  * CONCEPT User's Guide Ch. 5 (PM_gridsize, PM_scale, P3M_cutoff,
  * softeningfactors, boxsize) for the parameters. */

@@ -105,12 +105,24 @@ void begin_call(p3m_plan* P) {
 
 enum class Part { kP3M, kPM, kPP };
 
-// A one-sided plan evaluates small sets, and FP64 forces, from both sides all
-// the same (see kOneSidedMin).
-bool one_sided_call(const p3m_plan* P, int64_t n, bool vjp) {
-  if (P->rcap <= 0 || (!vjp && P->prm.precision != P3M_FP32)) return false;
+// Whether the plan's calls on n particles evaluate pairs of dense groups once,
+// given the partials (see kOneSidedMin). Small sets, and FP64 forces, are
+// evaluated from both sides all the same.
+bool one_sided_rule(const p3m_plan* P, int64_t n, bool vjp) {
+  if (P->prm.pair_partials <= 0) return false;
+  if (vjp ? !P->prm.adjoint : P->prm.precision != P3M_FP32) return false;
   if (P->one_sided_above >= 0) return n > P->one_sided_above;
   return n > (vjp ? kOneSidedVjpMin : kOneSidedMin);
+}
+
+// Whether any of the plan's calls is one-sided: only then it holds partials
+// (the rule holds for more particles if it holds for n).
+bool one_sided_plan(const p3m_plan* P) {
+  return one_sided_rule(P, P->n_max, false) || one_sided_rule(P, P->n_max, true);
+}
+
+bool one_sided_call(const p3m_plan* P, int64_t n, bool vjp) {
+  return P->rcap > 0 && one_sided_rule(P, n, vjp);
 }
 
 // Launches that take the plan's stream enqueue on `s` while this is alive.
@@ -612,7 +624,7 @@ int plan_geometry(const p3m_params& q, int64_t n_max, p3m_plan* P) {
   P->nrows = stencil_rows(P->G, r_c / h, nullptr, 0);
   if (P->nrows < 0) return P->nrows;
   P->nseg = P->npos = 0;
-  if (q.pair_partials > 0) P->nseg = segment_rows(P->G, r_c / h, nullptr, 0, &P->npos);
+  if (one_sided_plan(P)) P->nseg = segment_rows(P->G, r_c / h, nullptr, 0, &P->npos);
   if (P->nseg < 0) return P->nseg;
   P->max_items = P->ngroup + n_max / kMinChunk;
   return P3M_OK;
@@ -827,10 +839,9 @@ int p3m_plan_create_one_sided(const p3m_params* prm, int64_t n_max, int64_t abov
     W.lam_grid = dev_alloc<unsigned char>(3 * P->ncell * real, err);
   }
   // the one-sided pair sum: half stencil, per-group offsets, partials; if the
-  // partials do not fit, the plan sums every pair from both sides (an FP64
-  // plan's forces do in any case: only its adjoints take partials)
-  if (err == hipSuccess && q.pair_partials > 0 && P->npos > 0 &&
-      (q.precision == P3M_FP32 || q.adjoint)) {
+  // partials do not fit, the plan sums every pair from both sides (npos is 0
+  // in a plan none of whose calls is one-sided)
+  if (err == hipSuccess && P->npos > 0) {
     W.segrows = dev_alloc<int4>(P->nseg, err);
     W.prows = dev_alloc<int4>(P->npos, err);
     W.pbrows = dev_alloc<int4>(P->npos, err);

@@ -14,6 +14,7 @@ import functools
 
 import numpy as np
 import pytest
+import torch
 
 from oracle import adjoint, metrics
 from oracle import pm as o_pm
@@ -192,3 +193,24 @@ def test_smaller_groups(n, edge, partials):
             assert ran_one_sided(P, 2)
         assert metrics.force_errors(F, ref)["rms"] <= tol
         assert metrics.force_errors(g, ref_v)["rms"] <= vjp_tol
+
+
+@pytest.mark.parametrize("precision,adj,n,holds", [
+    ("fp32", False, 3 << 20, False), ("fp32", False, (3 << 20) + 1, True),
+    ("fp64", False, (3 << 20) + 1, False), ("fp32", True, 5 << 19, False),
+    ("fp64", True, 5 << 19, False), ("fp64", True, (5 << 19) + 1, True)])
+def test_partials_are_held_only_where_a_call_takes_them(precision, adj, n, holds):
+    """A plan none of whose calls is one-sided takes no memory for partials."""
+    from paper_1510_07621_amd import binding
+
+    def taken(partials):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        with binding.Plan(binding.Params(grid_n=64, precision=precision, adjoint=adj,
+                                         pair_partials=partials), n):
+            return before - torch.cuda.mem_get_info()[0]
+
+    taken(0)                                # (what the runtime keeps of its own)
+    extra = taken(80) - taken(0)
+    size = 80 * n * 3 * (4 if precision == "fp32" else 8)
+    assert extra >= size if holds else extra < size // 50
