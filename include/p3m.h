@@ -83,8 +83,11 @@ typedef struct p3m_params {
                              clustered sets); a call that needs more falls back
                              to both sides, and so do FP64 forces, FP32 forces on
                              up to 3 2^20 and adjoints of up to 5 2^19 particles,
-                             where both sides are faster. Pays on large clustered sets (256^3
-                             Plummer mix: -11 %), not on smooth ones            */
+                             where both sides are faster (sets of at least 6 a
+                             cell: up to 3 2^19, if the partials suffice for a
+                             uniform set). Pays on large clustered or crowded
+                             sets (256^3 Plummer mix: -13 %), not on smooth ones
+                             of a particle a cell                               */
 } p3m_params;
 
 /* Opaque plan: derived geometry, device workspace, and optional stage timers. */

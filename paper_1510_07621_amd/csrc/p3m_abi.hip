@@ -105,6 +105,31 @@ void begin_call(p3m_plan* P) {
 
 enum class Part { kP3M, kPM, kPP };
 
+// The reaction partials a plan with pair_partials > 0 holds.
+int64_t partials_cap(const p3m_plan* P) {
+  return (int64_t)P->prm.pair_partials * std::max<int64_t>(P->n_max, 1) + kPartialsSlack;
+}
+
+// The fewest particles of a crowded set (see kCrowdedMin).
+int64_t crowded_from(const p3m_plan* P) {
+  return std::max(kCrowdedMin + 1, kCrowdedPerCell * P->ncell);
+}
+
+// A crowded set whose partials fit if it is uniform: every item of a group
+// leaves one for each particle of the positive segments and, on average, for
+// half of its group (a group of Poisson size m has P(size > 64 k) items more
+// for each k; counted on uniform sets: 177 a particle at 8 a cell in groups of
+// 2^3, 181 by this; 241 and 241 at 11.4).
+bool crowded(const p3m_plan* P, int64_t n) {
+  if (n < crowded_from(P)) return false;
+  const double group = (double)n / P->ngroup;
+  double items = 1;
+  for (int64_t k = kChunk; k < group + 6 * std::sqrt(group); k += kChunk)
+    items += 0.5 * std::erfc((k - group) / std::sqrt(2 * group));
+  const double need = P->ngroup * items * ((double)P->pos_cells * n / P->ncell + 0.5 * group);
+  return need <= (double)partials_cap(P);
+}
+
 // Whether the plan's calls on n particles evaluate pairs of dense groups once,
 // given the partials (see kOneSidedMin). Small sets, and FP64 forces, are
 // evaluated from both sides all the same.
@@ -112,13 +137,16 @@ bool one_sided_rule(const p3m_plan* P, int64_t n, bool vjp) {
   if (P->prm.pair_partials <= 0) return false;
   if (vjp ? !P->prm.adjoint : P->prm.precision != P3M_FP32) return false;
   if (P->one_sided_above >= 0) return n > P->one_sided_above;
-  return n > (vjp ? kOneSidedVjpMin : kOneSidedMin);
+  return n > (vjp ? kOneSidedVjpMin : kOneSidedMin) || crowded(P, n);
 }
 
-// Whether any of the plan's calls is one-sided: only then it holds partials
-// (the rule holds for more particles if it holds for n).
+// Whether any of the plan's calls is one-sided: only then it holds partials.
+// (The lines hold for n_max if they hold for fewer; of the crowded sets the
+// smallest needs the fewest partials.)
 bool one_sided_plan(const p3m_plan* P) {
-  return one_sided_rule(P, P->n_max, false) || one_sided_rule(P, P->n_max, true);
+  for (const int64_t n : {P->n_max, std::min(P->n_max, crowded_from(P))})
+    if (one_sided_rule(P, n, false) || one_sided_rule(P, n, true)) return true;
+  return false;
 }
 
 bool one_sided_call(const p3m_plan* P, int64_t n, bool vjp) {
@@ -543,7 +571,8 @@ int stencil_rows(int g, double radius_cells, int32_t* out, int cap) {
   return stencil_rows_of(g, radius_cells, false, out, cap);
 }
 
-int segment_rows(int g, double radius_cells, int32_t* out, int cap, int* npos) {
+int segment_rows(int g, double radius_cells, int32_t* out, int cap, int* npos,
+                 int64_t* pos_cells) {
   const int nfull = stencil_rows_of(g, radius_cells, false, nullptr, 0);
   if (nfull < 0) return nfull;
   const double R = radius_cells + 1e-9;
@@ -551,6 +580,7 @@ int segment_rows(int g, double radius_cells, int32_t* out, int cap, int* npos) {
   const int reach = (int)std::ceil(R) + 1;
   auto gof = [g](int d) { return d >= 0 ? d / g : -((-d + g - 1) / g); };
   int count = 0, pos = 0;
+  int64_t cells = 0;
   // the full stencil's rows in their order (as stencil_rows_of walks them),
   // each cut where its z range crosses a group boundary
   for (int dx = -reach; dx < g + reach; ++dx) {
@@ -580,11 +610,15 @@ int segment_rows(int g, double radius_cells, int32_t* out, int cap, int* npos) {
           out[4 * count + 3] = sign;
         }
         ++count;
-        pos += sign > 0;
+        if (sign > 0) {
+          ++pos;
+          cells += zhi - zlo + 1;
+        }
       }
     }
   }
   if (npos) *npos = pos;
+  if (pos_cells) *pos_cells = cells;
   return count;
 }
 
@@ -624,8 +658,15 @@ int plan_geometry(const p3m_params& q, int64_t n_max, p3m_plan* P) {
   P->nrows = stencil_rows(P->G, r_c / h, nullptr, 0);
   if (P->nrows < 0) return P->nrows;
   P->nseg = P->npos = 0;
-  if (one_sided_plan(P)) P->nseg = segment_rows(P->G, r_c / h, nullptr, 0, &P->npos);
-  if (P->nseg < 0) return P->nseg;
+  if (q.pair_partials > 0 && (n_max > kCrowdedMin || P->one_sided_above >= 0)) {
+    int npos = 0;
+    const int nseg = segment_rows(P->G, r_c / h, nullptr, 0, &npos, &P->pos_cells);
+    if (nseg < 0) return nseg;
+    if (one_sided_plan(P)) {
+      P->nseg = nseg;
+      P->npos = npos;
+    }
+  }
   P->max_items = P->ngroup + n_max / kMinChunk;
   return P3M_OK;
 }
@@ -852,7 +893,7 @@ int p3m_plan_create_one_sided(const p3m_params* prm, int64_t n_max, int64_t abov
     W.gtot = dev_alloc<long long>(P->ngroup, err);
     W.gbase = dev_alloc<long long>(P->ngroup + 1, err);
     W.gscan_tmp = dev_alloc<long long>(react_scan_tmp_size(P->ngroup), err);
-    const int64_t cap = (int64_t)q.pair_partials * nn + kPartialsSlack;
+    const int64_t cap = partials_cap(P);
     if (err == hipSuccess) {
       void* p = nullptr;
       if (hipMalloc(&p, (size_t)cap * 3 * real) == hipSuccess) {

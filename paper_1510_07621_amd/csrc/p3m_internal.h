@@ -37,6 +37,16 @@ constexpr int kMinChunk = 16;     // the smallest chunk that small sets are cut 
 // 9.10, 8.93 and 22.4, 21.0.
 constexpr int64_t kOneSidedMin = int64_t{3} << 20;
 constexpr int64_t kOneSidedVjpMin = int64_t{5} << 19;
+// Crowded sets, whose pairs take longer than their partials, are one-sided
+// already above this many particles at this many a cell, if the plan's
+// partials suffice for a uniform set (a call that needs more would sum
+// from both sides in uncut items). Two- against one-sided, ms, uniform and
+// clustered: 2M on 64^3 FP32 12.5, 9.8 and 12.4, 12.1, FP32 adjoint 20.2, 15.8
+// and 20.4, 20.1, FP64 46.5, 38.1 and 47.5, 48.5; 1.7M on 64^3 FP32 8.7, 7.0
+// and 8.7, 8.9; 1.5M on 32^3 45.4, 33.7 and 43.7, 41.5. Below: 1.25M on 64^3
+// FP32 5.1, 5.2 and 5.0, 5.6; 360001 on 32^3 3.14, 3.13 and 2.97, 3.32.
+constexpr int64_t kCrowdedMin = int64_t{3} << 19;
+constexpr int64_t kCrowdedPerCell = 6;
 constexpr int kXcds = 8;          // accelerator complex dies of an MI355X (one L2 each)
 constexpr int kSplitBins = 64;    // pieces of the split-factor tables
 constexpr int kSplitCoef64 = 7;   // coefficients per piece of the FP64 table (degree 6)
@@ -140,6 +150,7 @@ struct p3m_plan {
   int64_t ngroup = 0;
   int nrows = 0;
   int nseg = 0, npos = 0;       // stencil segments, and the positive ones
+  int64_t pos_cells = 0;        // cells of the positive segments
   int64_t rcap = 0;             // reaction partials the plan holds (0: two-sided sum only)
   int64_t one_sided_above = -1; // one-sided calls on more particles than this (-1: the
                                 // library's lines, kOneSidedMin and kOneSidedVjpMin)
@@ -256,7 +267,8 @@ int stencil_rows(int g, double radius_cells, int32_t* out, int cap);
 // with the sign of that offset in lexicographic order (0: the group itself).
 // Entries (dx & 0xffff | dy << 16, dz_lo, dz_hi, sign); returns the count
 // (and the positive count in *npos).
-int segment_rows(int g, double radius_cells, int32_t* out, int cap, int* npos);
+int segment_rows(int g, double radius_cells, int32_t* out, int cap, int* npos,
+                 int64_t* pos_cells = nullptr);
 // Validation of the parameters (the checks and status codes of
 // p3m_plan_create) and the plan's geometry: grid, split and cutoff lengths,
 // i-group edge, stencil row count, work-list bound. Allocates nothing.

@@ -206,7 +206,7 @@ def test_partials_are_held_only_where_a_call_takes_them(precision, adj, n, holds
     def taken(partials):
         torch.cuda.synchronize()
         before = torch.cuda.mem_get_info()[0]
-        with binding.Plan(binding.Params(grid_n=64, precision=precision, adjoint=adj,
+        with binding.Plan(binding.Params(grid_n=128, precision=precision, adjoint=adj,
                                          pair_partials=partials), n):
             return before - torch.cuda.mem_get_info()[0]
 
@@ -214,3 +214,26 @@ def test_partials_are_held_only_where_a_call_takes_them(precision, adj, n, holds
     extra = taken(80) - taken(0)
     size = 80 * n * 3 * (4 if precision == "fp32" else 8)
     assert extra >= size if holds else extra < size // 50
+
+
+@pytest.mark.parametrize("kind,tol", [("force", 1e-5), ("vjp", 1e-4)])
+@pytest.mark.parametrize("grid,n,partials,one_sided", [
+    (64, 3 << 19, 140, False), (64, (3 << 19) + 1, 140, True), (64, (3 << 19) + 1, 60, False),
+    (128, (3 << 19) + 1, 140, False), (32, (3 << 19) + 1, 300, True)])
+def test_crowded_sets_are_one_sided_from_fewer_particles(grid, n, partials, one_sided, kind, tol):
+    """Both sides of the crowded sets' line, by particles, by particles a cell
+    and by partials: the route, and the result against the two-sided sum's."""
+    from paper_1510_07621_amd import binding
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + grid)
+    x = torch.rand((3, n), generator=gen, dtype=torch.float64, device="cuda")
+    lam = torch.randn((3, n), generator=gen, dtype=torch.float64, device="cuda")
+    prm = dict(grid_n=grid, precision="fp32", softening=0.02 / grid, adjoint=kind == "vjp",
+               rs_cells=1.0, cutoff_rs=4.5 if grid > 32 else 3.0)
+    out = []
+    for pp in (0, partials):
+        with binding.Plan(binding.Params(pair_partials=pp, **prm), n) as P:
+            P.set_timing(1)
+            out.append(P.pp_force(x, 1.0 / n) if kind == "force" else P.pp_force_vjp(x, 1.0 / n, lam))
+            assert (P.stage_times()[1]["react"] > 0) == (pp > 0 and one_sided)
+    assert ((out[1] - out[0]).norm() <= tol * out[0].norm()).item()
