@@ -132,13 +132,6 @@ __device__ __forceinline__ double3 ewald_corr(const double2* __restrict__ zp, in
   return c;
 }
 
-// 1 / sqrt(q), q > 0: the hardware estimate and one third-order step.
-__device__ __forceinline__ double rsqrt_pos(double q) {
-  const double y = __builtin_amdgcn_rsq(q);
-  const double e = fma(-q * y, y, 1.0);
-  return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
 __device__ __forceinline__ double min_image(double d, double box, double inv_box) {
   return d - box * rint(d * inv_box);
 }

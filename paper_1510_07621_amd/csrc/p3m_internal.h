@@ -59,9 +59,6 @@ constexpr int kMaxGrid = 512;          // cells per side of the largest grid
 // (With the odd ng/2 + 1 as stride each chunk of a row read by the y and x
 // passes straddled two cache lines.)
 __host__ __device__ inline int spec_stride(int ng) { return ((ng >> 1) + 1 + 15) & ~15; }
-// Reaction partials a plan holds for the one-sided pair sum by default, per
-// particle and in all (the 256^3 Plummer mix writes 56 per particle).
-constexpr int64_t kPartialsPerParticle = 80;
 // A group is dense (pairs with other dense groups evaluated once) above
 // this many particles. Measured on the clustered 256^3 set (FP32 pair
 // kernel + gather per force call): above 48 particles 31.5 + 4.3 ms, above 32
@@ -75,7 +72,20 @@ constexpr int64_t kPartialsPerParticle = 80;
 #define P3M_DENSE_MIN 32
 #endif
 constexpr int kDenseMin = P3M_DENSE_MIN;
+// Partials a one-sided plan holds besides pair_partials per particle (the 256^3
+// Plummer mix writes 56 per particle).
 constexpr int64_t kPartialsSlack = 65536;
+
+// 1 / sqrt(q) to FP64 rounding for q > 0: the hardware estimate refined by
+// one third-order step, y (1 + e/2 + 3e^2/8) with e = 1 - q y^2 (cubic
+// convergence from its roughly 23 correct bits). No fix-ups for zero,
+// infinite or negative q: callers keep q = 0 (a pair at zero separation
+// without softening) away or discard its weight.
+__device__ __forceinline__ double rsqrt_pos(double q) {
+  const double y = __builtin_amdgcn_rsq(q);
+  const double e = fma(-q * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
 
 // One particle in cell order: offsets from its cell's lower corner and mass.
 // (x, y, z, m) as float4 (FP32 path) or double4 (FP64 path).

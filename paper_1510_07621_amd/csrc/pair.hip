@@ -165,17 +165,6 @@ __device__ __attribute__((noinline)) double split_f64_series(double r2, double i
   return 1.0 - 2.2567583341910251 * (sqrt(r2) * inv2rs) * s * p;
 }
 
-// 1 / sqrt(q) to FP64 rounding for q > 0: the hardware estimate refined by
-// one third-order step, y (1 + e/2 + 3e^2/8) with e = 1 - q y^2 (cubic
-// convergence from its roughly 23 correct bits). No fix-ups for zero,
-// infinite or negative q: the only such case, q = 0 (a self pair without
-// softening), has its weight discarded by the caller.
-__device__ __forceinline__ double rsqrt_pos(double q) {
-  const double y = __builtin_amdgcn_rsq(q);
-  const double e = fma(-q * y, y, 1.0);
-  return fma(y * e, fma(e, 0.375, 0.5), y);
-}
-
 // FP64 split factor f from the table. TAB 1: the variable is the softened
 // distance rho = q rsqrt(q), q = r^2 + eps^2 (no square root); the few
 // leading pieces next to the kink at r = 0 that a polynomial cannot follow to
