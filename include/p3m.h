@@ -106,9 +106,13 @@ int p3m_params_default(p3m_params* out, int32_t grid_n, double box);
  * rs_cells <= 0, cutoff_rs <= 0, softening < 0, adjoint not 0 or 1,
  * ewald_gridsize not 0 or even in 8..512,
  * n_max < 0 or n_max >= 2^31; ERANGE when r_c >= box/2), then allocates the
- * workspace (with adjoint = 1 also that of the VJP calls: one more real grid,
- * three cotangent grids and a sorted cotangent array; with pair_partials > 0,
- * if a call on n_max particles may evaluate pairs once, the reaction
+ * workspace (per particle 45 bytes in FP32 and 77 in FP64, per cell 12 bytes
+ * and two to three reals, per i-group 8 bytes; with adjoint = 1 also that of
+ * the VJP calls: one more real grid, three cotangent grids, a sorted cotangent
+ * array and a cell index per particle; with ewald_gridsize = E > 0 the table,
+ * (E / 2 + 1)^3 nodes of 80 bytes, and the pair sum's partial sums, 1.5 KB per
+ * particle up to 32768 particles, 201 MB from 65536 on; with pair_partials > 0,
+ * if a call on n_max or fewer particles may evaluate pairs once, the reaction
  * partials, pair_partials n_max + 65536 of 3 reals each (at 80: 0.96 KB (FP32)
  * or 1.9 KB (FP64) per particle), plus per-group offsets; if that allocation
  * fails the plan evaluates every pair from both sides)
@@ -349,8 +353,10 @@ int p3m_stage_times(p3m_plan* plan, double* ms_out, int32_t n_stages);
  * one fixed device array of 12 MiB per GPU, held from the library's first
  * such call on that GPU until the process ends; the stencil rows and the
  * split-factor table are computed on the host (the last parameters' are
- * kept) and written into it by a kernel on hip_stream that carries them in
- * its arguments, before the other kernels run.
+ * kept: calls that alternate between sets compute them each time, 0.2 ms in
+ * FP32 and 0.6 ms in FP64) and written into it by one to six kernels on
+ * hip_stream that carry them in their arguments, before the other kernels
+ * run.
  *   params      as for p3m_plan_create (all of it validated the same way;
  *               fd_order, deconv_power, adjoint and ewald_gridsize unused)
  *   n           0 <= n <= P3M_NOALLOC_MAX_N

@@ -265,8 +265,8 @@ class Params:
     deconv_power: int = 2
     adjoint: bool = False        # also allocate the workspace of the VJP calls
     ewald_gridsize: int = 0      # > 0: tabulate the Ewald correction (pp_ewald_force)
-    pair_partials: int = 0       # < 0: every pair from both sides; else partials per
-                                 # particle of the one-sided sum (0: the default)
+    pair_partials: int = 0       # partials per particle of the one-sided sum (0: every
+                                 # pair from both sides)
 
     def to_c(self) -> P3MParams:
         if self.precision not in ("fp32", "fp64"):

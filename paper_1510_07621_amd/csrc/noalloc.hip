@@ -3,7 +3,9 @@
 // stencil rows, split tables, sorted records) is carved from one file-scope
 // device array of fixed size; the stencil and the split table are computed
 // on the host (once while the parameters stay) and handed over in the
-// arguments of the call's first kernel. The arithmetic
+// arguments of the call's first kernels, 960 words each: one launch for the 260
+// words of an FP32 table and up to 700 stencil rows (one word a row), two for
+// an FP64 table's 910 words and more than 50 rows, at most six. The arithmetic
 // is that of pp_force (the same kernels), with every pair evaluated from
 // both sides.
 #include <cmath>

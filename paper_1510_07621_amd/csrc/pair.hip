@@ -54,8 +54,12 @@ constexpr int kDesc = 3 * 64;          // runs per batch of 64 rows
 constexpr int kNoReaction = -2147483647 - 1;
 // j-particles staged in LDS per pass: kPairCap for the FP32 force, half that
 // for FP64 and for the adjoint (which stages the cotangents too), so that the
-// workgroup's LDS leaves room for the waves per SIMD that its registers allow:
-// FP32 5.0 KB, adjoint 4.8 KB and FP64 7.4 KB, 5 waves; FP64 adjoint 9.5 KB, 4.
+// workgroup's LDS leaves room for the waves per SIMD that its registers allow
+// (two-sided, one wave an item; waves per SIMD as the compiler reports them):
+// FP32 5.1 KB and its adjoint 4.8 KB, 5 waves; FP64 7.5 KB, 5 with one mass over
+// the softened-distance table (96 VGPRs), else 4 (100 to 108); FP64 adjoint 9.5
+// KB, 4 over that table (123 to 128), but 3 with masses of their own where waves
+// share items (129), and over r (146 to 150).
 // (FP32, 192 entries: 128^3 lattice 2.25 -> 2.21 ms, but sparse sets 240 ->
 // 246 us and the one-sided sum 30.8 -> 31.0 ms; 256: 34.0 ms at 4 waves. FP32
 // adjoint, 128 entries: 4.04 -> 4.30 ms.)
@@ -66,9 +70,10 @@ template <typename T, bool VJP> struct Stage {
 // At most kStreams streams (without clamped reads), so kStreams far sentinels
 // after the staged entries cover every read past the end.
 constexpr int kStreams = 16;
-// Waves per SIMD the compiler must leave room for (caps the registers; FP64
-// and the adjoints fit in one more without being asked, and asking cost them
-// up to 4 %).
+// Waves per SIMD the compiler must leave room for (caps the registers). The
+// FP32 adjoint from both sides, FP64 with one mass and its adjoint over the
+// softened-distance table fit in one more without being asked, and asking cost
+// them up to 4 %; the other instantiations of FP64 do not.
 template <typename T, bool VJP>
 constexpr int kPairWaves = sizeof(T) == 4 ? (VJP ? 4 : 5) : (VJP ? 3 : 4);
 // A coordinate far outside any box: its squared separation from any real
@@ -420,9 +425,9 @@ constexpr bool Clamped = !HALF && (sizeof(T) == 8 || VJP);
 // One wave's staging area. Its size sets the waves in flight (LDS is handed
 // out in 1280-byte pieces). With a run's offsets in one word beside its slot
 // instead of five arrays, the owners in the entries' place and one sentinel
-// where reads are clamped, the two-sided FP64 sum went from 9.5 to 7.4 KB (4
-// to 5 waves per SIMD) and its adjoint from 12.0 to 9.5 KB (3 to 4). With the
-// scans by DPP: 128^3 lattice FP32 2.35 -> 2.25 ms, FP64 6.02 -> 5.54 ms; 64^3
+// where reads are clamped, the two-sided FP64 sum went from 9.5 to 7.5 KB (4
+// to 5 waves per SIMD with one mass) and its adjoint from 12.0 to 9.5 KB (3 to
+// 4). With the scans by DPP: 128^3 lattice FP32 2.35 -> 2.25 ms, FP64 6.02 -> 5.54 ms; 64^3
 // FP64 adjoint 1.55 -> 1.28 ms; one-sided 256^3 31.9 -> 31.0 ms.
 template <typename T, bool VJP, bool HALF>
 struct WaveShared {
