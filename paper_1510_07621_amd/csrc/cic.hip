@@ -35,7 +35,7 @@ using namespace brick;
 // average) and its weights are formed once. (A node that looped over the
 // particles of its eight cells read and weighted each particle eight times:
 // 256^3 lattice FP32 362 -> 185 us, clustered 862 -> 373; the cotangent's
-// deposit on 2M clustered particles 697 -> 213. What is left is the loop over
+// deposit on 2M clustered particles, FP32, 697 -> 213. What is left is the loop over
 // a cell's particles, as long as the wave's fullest cell.) NC = 1: mass, scaled by 1 / h^3
 // (the density); NC = 3: mass times each component of a cotangent (the
 // adjoint's deposit), unscaled, to out[c * ng^3 + node].
